@@ -269,6 +269,7 @@ struct dgmi_mlp {
   float *adam_v = nullptr;   // second moments
   float *partial = nullptr;  // per-block gradient partials
   float *loss = nullptr;     // scratch for the loss partials
+  double *fit = nullptr;     // per-block sums of mlp_fit_normalization
   int64_t partial_cap = 0;   // blocks the partial buffer holds
   int64_t step = 0;          // Adam step count
   int device = 0;
