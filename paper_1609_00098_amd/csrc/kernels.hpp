@@ -267,10 +267,8 @@ struct dgmi_mlp {
   float *grad = nullptr;     // kNumWeights floats
   float *adam_m = nullptr;   // first moments
   float *adam_v = nullptr;   // second moments
-  float *partial = nullptr;  // per-block gradient partials
-  float *loss = nullptr;     // scratch for the loss partials
+  float *partial = nullptr;  // per-workgroup rows of gradient and squared-error sums
   double *fit = nullptr;     // per-block sums of mlp_fit_normalization
-  int64_t partial_cap = 0;   // blocks the partial buffer holds
   int64_t step = 0;          // Adam step count
   int device = 0;
 };

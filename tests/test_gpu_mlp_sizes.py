@@ -41,3 +41,56 @@ def test_normalization_sizes(dg, n):
     got_mean, got_sd = np.append(p[M.O_MU:M.O_MU + 5], p[M.O_YMU]), np.append(p[M.O_SD:M.O_SD + 5], p[M.O_YSD])
     assert np.all(np.abs(got_mean - mean) <= 2e-7 * np.abs(mean) + 1e-12 * sd)
     assert np.all(np.abs(got_sd - sd) <= 2e-7 * sd)
+
+
+def _batch(n):
+    rng = np.random.default_rng(n)
+    p = np.zeros(M.NP, dtype=np.float32)
+    p[:M.NW] = rng.uniform(-0.3, 0.3, M.NW)
+    x = rng.normal(size=(5, n)).astype(np.float32)
+    t = (x[0] - 0.5 * x[4] + 0.1 * rng.normal(size=n)).astype(np.float32)
+    p[M.O_SD:M.O_SD + 5] = 1.0
+    p[M.O_YSD] = 1.0
+    return p, x, t
+
+
+# tiles of 32 samples; 512 workgroups from 16,384 samples on, then a second
+# tile for some, for all, and a ragged last one
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 200, 4096, 16_384, 16_385, 33_000])
+def test_gradient_sizes(dg, n):
+    """Gradients and loss of a batch in a wider matrix against FP64
+    back-propagation: FP32 sums of products with relative errors of a few
+    2^-24 each, at most 1e-5 relative Frobenius per tensor (the bound the
+    fixed-batch test holds); bit-identical on a second evaluation."""
+    import torch
+    p, x, t = _batch(n)
+    net = dg.Mlp(seed=0)
+    dg.mlp_set(net, to_dev(p))
+    wide = torch.full((5, n + 5), float("nan"), dtype=torch.float32, device="cuda")
+    wide[:, 2:2 + n] = to_dev(x)
+    g, loss = dg.mlp_grad(net, wide[:, 2:2 + n], to_dev(t))
+    Lo, go = M.loss_and_grad(p.astype(np.float64), x.astype(np.float64), t.astype(np.float64))
+    gh = to_host(g).astype(np.float64)
+    assert abs(float(to_host(loss)[0]) - Lo) <= 1e-5 * Lo
+    for a, b in ((M.O_W1, M.O_B1), (M.O_B1, M.O_W2), (M.O_W2, M.O_B2), (M.O_B2, M.O_W3), (M.O_W3, M.O_B3), (M.O_B3, M.NW)):
+        assert np.linalg.norm(gh[a:b] - go[a:b]) <= 1e-5 * np.linalg.norm(go[a:b])
+    g2, loss2 = dg.mlp_grad(net, wide[:, 2:2 + n], to_dev(t))
+    assert np.array_equal(to_host(g2), to_host(g)) and np.array_equal(to_host(loss2), to_host(loss))
+
+
+def test_train_step_is_gradient_then_adam(dg):
+    """The update fused into the reduction equals Adam applied to mlp_grad's
+    gradient (two steps; FP32 arithmetic against FP64: 2e-3 of a step, as
+    gradients near zero pass through g / (|g| + 1e-8))."""
+    p, x, t = _batch(2048)
+    net, ref = dg.Mlp(seed=0), dg.Mlp(seed=0)
+    dg.mlp_set(net, to_dev(p))
+    q, m, v = p.astype(np.float64), np.zeros(M.NW), np.zeros(M.NW)
+    lr = 1e-3
+    for k in (1, 2):
+        dg.mlp_set(ref, dg.mlp_get(net))
+        g, loss_g = dg.mlp_grad(ref, to_dev(x), to_dev(t))
+        loss = dg.mlp_train_step(net, to_dev(x), to_dev(t), lr)
+        assert np.array_equal(to_host(loss), to_host(loss_g))
+        q, m, v = M.adam_step(q, to_host(g).astype(np.float64), m, v, k, lr)
+        assert np.abs(to_host(dg.mlp_get(net)) - q).max() <= 2e-3 * lr + 2.0 ** -23
