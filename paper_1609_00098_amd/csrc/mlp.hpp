@@ -34,16 +34,6 @@ constexpr int kOffYmu = kOffSd + kIn;      // 4619
 constexpr int kOffYsd = kOffYmu + 1;       // 4620
 constexpr int kNumParams = kOffYsd + 1;    // 4621
 
-struct MlpSmem {
-  alignas(16) float w[kNumParams + 3];
-};
-
-__device__ __forceinline__ void mlp_load_smem(const float *p, MlpSmem *s) {
-  for (int t = threadIdx.x; t < kNumParams; t += blockDim.x) s->w[t] = p[t];
-}
-
-__device__ __forceinline__ float silu_f(float x) { return x / (1.0f + __expf(-x)); }
-
 // Raw (un-normalised) features of a conserved state; B = 0 for hydro.  The
 // last one is the pressure function at zero pressure, (g-1) rho eps(0): the
 // thermal energy left once the kinetic and magnetic parts are accounted for
@@ -67,65 +57,73 @@ __host__ __device__ __forceinline__ void mlp_features(const double *u, double g,
   x[4] = (float)log(f0 / D);
 }
 
-// Forward pass for one normalised input; returns the normalised output.
-__device__ __forceinline__ float mlp_forward_one(const float *w, const float *xn) {
-  float h1[kH];
-#pragma unroll
-  for (int j = 0; j < kH; ++j) {
-    float a = w[kOffB1 + j];
-#pragma unroll
-    for (int i = 0; i < kIn; ++i) a += w[kOffW1 + j * kIn + i] * xn[i];
-    h1[j] = silu_f(a);
-    // keep the weight loads next to their use (no hoisting of all 384 loads)
-    if ((j & 7) == 7) __builtin_amdgcn_sched_barrier(0);
-  }
-  float y = w[kOffB3];
-#pragma unroll 1
-  for (int j = 0; j < kH; ++j) {
-    const float4 *row = reinterpret_cast<const float4 *>(w + kOffW2 + j * kH);
-    float a0 = w[kOffB2 + j], a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
-#pragma unroll
-    for (int i4 = 0; i4 < kH / 4; ++i4) {
-      const float4 r = row[i4];
-      a0 += r.x * h1[4 * i4];
-      a1 += r.y * h1[4 * i4 + 1];
-      a2 += r.z * h1[4 * i4 + 2];
-      a3 += r.w * h1[4 * i4 + 3];
-      if ((i4 & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-    }
-    y += w[kOffW3 + j] * silu_f((a0 + a1) + (a2 + a3));
-  }
-  return y;
-}
-
 // ---------------------------------------------------------------------
-// Recovery seed on the matrix cores, all in FP32.  One wave evaluates the
-// network for its 64 points together:
-//   layer 1 (5 -> 64) and its activations on the vector units, two hidden
-//     units at a time, each lane for its own point;
-//   layer 2 (the 64 x 64 product, 90% of the flops) as [64 points x 64] x
-//     [64 x 64] with v_mfma_f32_32x32x2_f32 (FP32 operands and accumulation),
-//     fed straight from registers: for k step ks the A operand of lane l is
-//     unit 2 ks + l / 32 of point l % 32 (+32 for the second row tile), so
-//     one exchange of the two half-waves per step supplies it;
-//   layer 3 as a per-point dot product, summed over the units the lanes of a
-//     half-wave hold by a butterfly of half-wave exchanges.
-// No per-wave LDS: the block shares only the weights.
+// Inference on the matrix cores.  A wave evaluates 32 samples at a time with
+// both layers transposed, [units x inputs] x [inputs x samples] in 32 x 32
+// tiles: the result of a product then holds, in lane l, the units
+// 8 q + 4 (l / 32) + c (q, c = 0 .. 3; + 32 per row tile) of sample l % 32, and
+// after the activation those entries are the very B operand (their units as
+// rows, column l % 32) of the next layer's product, if its A operand takes
+// the columns of W2 in the same order.  So activations never leave their
+// lane, the biases ride along (b1 as the weight of a sixth input 1, b2 as the
+// accumulators' start), and the output is a dot product in the lane and one
+// exchange of the two half-waves.
+//
+// Layer 1 (K = 6) runs on v_mfma_f32_32x32x2_f32.  Layer 2, 90% of the
+// arithmetic, runs on v_mfma_f32_32x32x16_bf16 with both operands split into
+// three bfloat16 parts each, x = hi + mid + lo to 2^-27 x, and the six products
+// of parts above 2^-25 accumulated in FP32, so that no accuracy is given up:
+// against FP64 the outputs are off by 2.2e-8 (2-norm, training distribution),
+// by 2.4e-8 with scalar FP32 sums.
+// In FP32 the products alone occupy a SIMD for 4,480 cycles per 32 samples and
+// do not run beside the vector unit's 2,800 cycles of activations (half of
+// them exp and reciprocal): 90 us for 10^6 samples.  Split, they take 1,920
+// cycles on cores the activations leave free: 62 us.
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float float2_t __attribute__((ext_vector_type(2)));
 
-struct MlpSeedShared {  // per block: the weights in FP32, W2 as operand fragments
-  float w1[kH * kIn], b1[kH], b2[kH], w3[kH], b3, mu[kIn], sd[kIn], ymu, ysd;
-  float2_t w2f[32][64];  // [k step][lane]: W2[l % 32][2 ks + l / 32], W2[l % 32 + 32][2 ks + l / 32]
+// x = f[0] + f[1] + f[2] + e with |e| <= 2^-27 |x|, for two values at once (the
+// conversion packs two), into the entries j and j + 1 of f
+__device__ __forceinline__ void split3(float2_t x, bf16x8_t *f, int j) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const bf16x2_t h = __builtin_convertvector(x, bf16x2_t);
+    f[i][j] = h[0];
+    f[i][j + 1] = h[1];
+    x[0] -= (float)h[0];
+    x[1] -= (float)h[1];
+  }
+}
+
+struct MlpNet {  // per block: the weights as the products read them
+  // W2 by A operand: [row tile m][column step k][lane][part], the eight columns
+  // of step k = 2 t + p in lane l being 32 t + 8 (2 p + j / 4) + 4 (l / 32) + j % 4
+  bf16x8_t w2[2][4][64][3];
+  alignas(16) float b2[kH], w3[kH];
+  float w1[kH][kIn + 1];  // W1, and b1 as the sixth column
+  float b3, mu[kIn], sd[kIn], ymu, ysd;
 };
 
-// Fills the block's shared weights.  The B operand of layer 2 is
-// B[k][n] = W2[n][k]; in the 32x32x2 layout lane l holds column n = l % 32
-// (+32 for the second column tile) at row k = 2 ks + l / 32.
-__device__ __forceinline__ void mlp_seed_load_shared(const float *p, MlpSeedShared *s) {
-  for (int t = threadIdx.x; t < kH * kIn; t += blockDim.x) s->w1[t] = p[kOffW1 + t];
+__device__ __forceinline__ void mlp_net_load(const float *p, MlpNet *s) {
+  for (int t = threadIdx.x; t < 2 * 4 * 64; t += blockDim.x) {
+    const int l = t & 63, k = (t >> 6) & 3, m = t >> 8;
+    const float *row = p + kOffW2 + (32 * m + (l & 31)) * kH + 32 * (k >> 1) + 16 * (k & 1) + 4 * (l >> 5);
+    bf16x8_t f[3];
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+      const int c = 8 * (j >> 2) + (j & 3);
+      split3(float2_t{row[c], row[c + 1]}, f, j);
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) s->w2[m][k][l][i] = f[i];
+  }
+  for (int t = threadIdx.x; t < kH * kIn; t += blockDim.x) s->w1[t / kIn][t % kIn] = p[kOffW1 + t];
   for (int t = threadIdx.x; t < kH; t += blockDim.x) {
-    s->b1[t] = p[kOffB1 + t];
+    s->w1[t][kIn] = p[kOffB1 + t];
     s->b2[t] = p[kOffB2 + t];
     s->w3[t] = p[kOffW3 + t];
   }
@@ -138,111 +136,100 @@ __device__ __forceinline__ void mlp_seed_load_shared(const float *p, MlpSeedShar
     s->ymu = p[kOffYmu];
     s->ysd = p[kOffYsd];
   }
-  for (int t = threadIdx.x; t < 32 * 64; t += blockDim.x) {
-    const int l = t & 63, ks = t >> 6;
-    const int k = 2 * ks + (l >> 5), n = l & 31;
-    float2_t b;
-    b[0] = p[kOffW2 + n * kH + k];
-    b[1] = p[kOffW2 + (n + 32) * kH + k];
-    s->w2f[ks][l] = b;
-  }
 }
 
-__device__ __forceinline__ float silu_seed(float x) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
+// x sigmoid(x), the reciprocal from the hardware estimate (within one ulp)
+__device__ __forceinline__ float silu_fast(float x) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
 
-// One step of a recursive-halving sum across lanes l and l ^ M: each keeps
-// the half of V[0 .. 2M) selected by bit M of its lane (moved to V[0 .. M))
-// plus the partner's copy of that half.
-template <int M>
-__device__ __forceinline__ void halving_step(float *V, int l) {
-  const bool keep_hi = (l & M) != 0;
+// Normalised output for 32 samples, all 64 lanes of the wave together: lane l
+// passes inputs l / 32, 2 + l / 32 and 4 + l / 32 (the sixth being 1) of sample
+// l % 32 and receives that sample's output.
+__device__ __forceinline__ float mlp_net32(const MlpNet *s, float x0, float x1, float x2) {
+  const int r = threadIdx.x & 31, h = (threadIdx.x >> 5) & 1;
+  const float xb[3] = {x0, x1, x2};
+  floatx16_t H[2], E[2];
+  // the weights are read from LDS where they are used (hoisted out of the
+  // caller's loop, as the compiler would, they take 130 registers)
+#define MLP_KEEP_LOADS() asm volatile("" ::: "memory")
+  MLP_KEEP_LOADS();
 #pragma unroll
-  for (int j = 0; j < M; ++j) {
-    const float mine = keep_hi ? V[j + M] : V[j];
-    const float send = keep_hi ? V[j] : V[j + M];
-    V[j] = mine + __shfl_xor(send, M);
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int a = 0; a < 16; ++a) H[m][a] = 0.0f;
+#pragma unroll
+  for (int ks = 0; ks < 3; ++ks)
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+      H[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(s->w1[32 * m + r][2 * ks + h], xb[ks], H[m], 0, 0, 0);
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4_t b = *reinterpret_cast<const float4_t *>(&s->b2[32 * m + 8 * q + 4 * h]);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) E[m][4 * q + c] = b[c];
+    }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    MLP_KEEP_LOADS();
+    const int l = threadIdx.x & 63;
+    bf16x8_t w[2][3], f[3];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) w[m][i] = s->w2[m][k][l][i];
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+      const int a = 8 * (k & 1) + j;
+      split3(float2_t{silu_fast(H[k >> 1][a]), silu_fast(H[k >> 1][a + 1])}, f, j);
+    }
+    // the smallest products first
+#pragma unroll
+    for (int o = 2; o >= 0; --o)
+#pragma unroll
+      for (int i = 0; i <= o; ++i)
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+          E[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[m][i], f[o - i], E[m], 0, 0, 0);
   }
+  MLP_KEEP_LOADS();
+#undef MLP_KEEP_LOADS
+  float y[2] = {0.0f, 0.0f};
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4_t w = *reinterpret_cast<const float4_t *>(&s->w3[32 * m + 8 * q + 4 * h]);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) y[m] += w[c] * silu_fast(E[m][4 * q + c]);
+    }
+  const float yl = y[0] + y[1];
+  return yl + __shfl_xor(yl, 32) + s->b3;
 }
 
-// Called by all 64 lanes of a wave together (every lane must take part);
-// returns this lane's seed D exp(y).
+// Recovery seed D exp(y) of this lane's point, all 64 lanes of a wave together
+// (every lane must take part): its points as two passes of 32.
 template <int SYS>
-__device__ __forceinline__ double mlp_seed_wave(const MlpSeedShared *s, const double *u, double g) {
-  const int l = threadIdx.x & 63;
-  const bool lo = l < 32;
+__device__ __forceinline__ double mlp_seed_wave(const MlpNet *s, const double *u, double g) {
+  const bool lo = (threadIdx.x & 63) < 32;
   float x[kIn];
   mlp_features<SYS>(u, g, x);
 #pragma unroll
   for (int i = 0; i < kIn; ++i) x[i] = (x[i] - s->mu[i]) / s->sd[i];
-  // C[rt][nt]: points 32 rt .. 32 rt + 31 against units 32 nt .. 32 nt + 31;
-  // entry a of lane l is point 8 (a / 4) + 4 (l / 32) + a % 4 (+ 32 rt) and
-  // unit l % 32 (+ 32 nt)
-  floatx16_t C00, C01, C10, C11;
-#pragma unroll
-  for (int a = 0; a < 16; ++a) {
-    C00[a] = 0.0f;
-    C01[a] = 0.0f;
-    C10[a] = 0.0f;
-    C11[a] = 0.0f;
-  }
+  // an input pair (k, k + 1): each half-wave needs its own row of the pair
+  // for both passes, the other half holds it for one of them
+  const float o0 = __shfl_xor(lo ? x[1] : x[0], 32), o1 = __shfl_xor(lo ? x[3] : x[2], 32), o2 = __shfl_xor(x[4], 32);
+  float y = 0.0f;
 #pragma unroll 1
-  for (int ks = 0; ks < 32; ++ks) {
-    // layer 1: units 2 ks and 2 ks + 1 of this lane's point
-    float h[2];
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int j = 2 * ks + c;
-      float a = s->b1[j];
-#pragma unroll
-      for (int i = 0; i < kIn; ++i) a += s->w1[j * kIn + i] * x[i];
-      h[c] = silu_seed(a);
-    }
-    // the other half-wave's unit: lanes < 32 need unit 2 ks of point l + 32,
-    // lanes >= 32 unit 2 ks + 1 of point l - 32
-    const float other = __shfl_xor(lo ? h[1] : h[0], 32);
-    const float A0 = lo ? h[0] : other;  // row tile 0: points 0..31
-    const float A1 = lo ? other : h[1];  // row tile 1: points 32..63
-    const float2_t B = s->w2f[ks][l];
-    C00 = __builtin_amdgcn_mfma_f32_32x32x2f32(A0, B[0], C00, 0, 0, 0);
-    C01 = __builtin_amdgcn_mfma_f32_32x32x2f32(A0, B[1], C01, 0, 0, 0);
-    C10 = __builtin_amdgcn_mfma_f32_32x32x2f32(A1, B[0], C10, 0, 0, 0);
-    C11 = __builtin_amdgcn_mfma_f32_32x32x2f32(A1, B[1], C11, 0, 0, 0);
+  for (int p = 0; p < 2; ++p) {  // (rolled: one pass's registers at a time)
+    const bool own = lo == (p == 0);
+    const float x0 = own ? (lo ? x[0] : x[1]) : o0, x1 = own ? (lo ? x[2] : x[3]) : o1;
+    const float yp = mlp_net32(s, x0, x1, lo ? (p == 0 ? x[4] : o2) : 1.0f);
+    if (own) y = yp;
   }
-  // layer 2 activations times the layer-3 weights, summed over this lane's
-  // two units: V[16 rt + a] belongs to point 32 rt + 8 (a / 4) + 4 (l / 32) + a % 4
-  const int n0 = l & 31, n1 = n0 + 32;
-  const float b20 = s->b2[n0], b21 = s->b2[n1], w30 = s->w3[n0], w31 = s->w3[n1];
-  float V[32];
-#pragma unroll
-  for (int a = 0; a < 16; ++a) {
-    V[a] = w30 * silu_seed(C00[a] + b20) + w31 * silu_seed(C01[a] + b21);
-    V[16 + a] = w30 * silu_seed(C10[a] + b20) + w31 * silu_seed(C11[a] + b21);
-  }
-  // sum over the 32 lanes of the half-wave (their units): recursive halving,
-  // after which lane l holds the full sum of entry l % 32
-  halving_step<16>(V, l);
-  halving_step<8>(V, l);
-  halving_step<4>(V, l);
-  halving_step<2>(V, l);
-  halving_step<1>(V, l);
-  // entry v = l % 32 of half-wave h = l / 32 is point 32 (v / 16) +
-  // 8 ((v % 16) / 4) + 4 h + v % 4; fetch this lane's own point
-  const int src = 32 * ((l >> 2) & 1) + 16 * (l >> 5) + 4 * ((l >> 3) & 3) + (l & 3);
-  const float ysum = __shfl(V[0], src);
-  const float y = (s->b3 + ysum) * s->ysd + s->ymu;
+  y = y * s->ysd + s->ymu;
   // the seed needs no more than FP32 (the FP64 iteration decides the result)
   return u[0] * (double)__expf(y);
-}
-
-template <int SYS>
-__device__ __forceinline__ double mlp_guess(const MlpSmem *s, const double *u, double g) {
-  float x[kIn];
-  mlp_features<SYS>(u, g, x);
-#pragma unroll
-  for (int i = 0; i < kIn; ++i) x[i] = (x[i] - s->w[kOffMu + i]) / s->w[kOffSd + i];
-  const float yn = mlp_forward_one(s->w, x);
-  const float y = yn * s->w[kOffYsd] + s->w[kOffYmu];
-  return u[0] * exp((double)y);
 }
 
 }  // namespace dgmi

@@ -7,16 +7,16 @@
 namespace dgmi {
 
 template <int SYS, int GUESS>
-__global__ void __launch_bounds__(256) con2prim_kernel(const C2PArgs A) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GUESS == 2 ? 4 : 1))) con2prim_kernel(const C2PArgs A) {
   constexpr int NV = SysTraits<SYS>::nv;
   const int64_t n = A.n;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   unsigned long long nbad = 0;
-  MlpSeedShared *sm = nullptr;
+  MlpNet *sm = nullptr;
   if (GUESS == 2) {
-    __shared__ MlpSeedShared smem;
+    __shared__ MlpNet smem;
     sm = &smem;
-    mlp_seed_load_shared(A.mlp, sm);
+    mlp_net_load(A.mlp, sm);
     __syncthreads();
   }
   // wave-uniform trip count (the learned seed runs all 64 lanes together)
@@ -40,6 +40,13 @@ __global__ void __launch_bounds__(256) con2prim_kernel(const C2PArgs A) {
     if (GUESS == 2) {
       p0 = mlp_seed_wave<SYS>(sm, u, A.gamma);
       extra = 1;  // the network's f(0) feature
+      // the state again, from L2, so that neither it nor what the features
+      // and the recovery share is held through the network
+      asm volatile("" ::: "memory");
+      if (valid) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) u[v] = A.U[v * n + q];
+      }
     }
     if (GUESS == 3 && valid) {
       // f(0): the thermal energy left at zero pressure, an estimate of p

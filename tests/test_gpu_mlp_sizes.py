@@ -94,3 +94,60 @@ def test_train_step_is_gradient_then_adam(dg):
         assert np.array_equal(to_host(loss), to_host(loss_g))
         q, m, v = M.adam_step(q, to_host(g).astype(np.float64), m, v, k, lr)
         assert np.abs(to_host(dg.mlp_get(net)) - q).max() <= 2e-3 * lr + 2.0 ** -23
+
+
+# a wave takes 32 samples, a workgroup 128, the grid 131,072 before it loops
+@pytest.mark.parametrize("n", [1, 31, 33, 127, 128, 129, 5000, 131_073, 140_001])
+def test_forward_sizes(dg, n):
+    """The network's output against FP64, columns of a wider matrix, nothing
+    written beyond them (bound of the fixed-size test: 2e-5 of the output's
+    scale for FP32 dot products of 64 terms in two layers)."""
+    import torch
+    p, x, _ = _batch(n)
+    net = dg.Mlp(seed=0)
+    dg.mlp_set(net, to_dev(p))
+    wide = torch.full((5, n + 9), float("nan"), dtype=torch.float32, device="cuda")
+    wide[:, 4:4 + n] = to_dev(x)
+    y = torch.full((n + 64,), -7.0, dtype=torch.float32, device="cuda")
+    dg.mlp_forward(net, wide[:, 4:4 + n], y[:n])
+    yo = M.predict(p.astype(np.float64), x.astype(np.float64))
+    yh = to_host(y)
+    assert np.abs(yh[:n] - yo).max() <= 2e-5 * max(1.0, np.abs(yo).max())
+    assert np.all(yh[n:] == -7.0)
+
+
+def test_forward_keeps_samples_apart(dg):
+    """A sample with NaN or infinite features leaves its neighbours alone."""
+    p, x, _ = _batch(200)
+    net = dg.Mlp(seed=0)
+    dg.mlp_set(net, to_dev(p))
+    clean = to_host(dg.mlp_forward(net, to_dev(x)))
+    x[2, 37], x[0, 64] = np.nan, np.inf
+    y = to_host(dg.mlp_forward(net, to_dev(x)))
+    keep = np.ones(200, dtype=bool)
+    keep[[37, 64]] = False
+    assert np.isnan(y[37]) and not np.isfinite(y[64]) and np.array_equal(y[keep], clean[keep])
+
+
+@pytest.mark.parametrize("system", [1, 2])
+@pytest.mark.parametrize("n", [1, 32, 63, 65, 300])
+def test_learned_seed_sizes(ora, dg, system, n):
+    """Recoveries seeded by the network at ragged sizes: the residual bound of
+    the tolerance mode at every point, nothing written beyond the points."""
+    import torch
+    from paper_1609_00098_amd import synth
+    g = 4.0 / 3.0
+    if system == 2:
+        prim, mag = synth.srmhd_samples(n, seed=n)
+    else:
+        prim, mag = synth.sr_samples(n, seed=n), None
+    U = ora.prim2cons(system, g, prim, mag)
+    p, _, _ = _batch(1)
+    net = dg.Mlp(seed=0)
+    dg.mlp_set(net, to_dev(p))
+    buf = torch.full((5 * n + 64,), -7.0, dtype=torch.float64, device="cuda")
+    P = buf[:5 * n].view(5, n)
+    fails = torch.zeros(1, dtype=torch.int64, device="cuda")
+    dg.con2prim(system, g, to_dev(U), P, guess=dg.GUESS_LEARNED, mlp=net, tol=1e-10, n_failed=fails)
+    assert int(fails.item()) == 0 and bool((buf[5 * n:] == -7.0).all())
+    assert ora.backward_residual(system, g, U, to_host(P)).max() <= 1e-10
