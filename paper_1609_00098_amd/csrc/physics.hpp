@@ -230,65 +230,80 @@ DG_HD void flux_all(const double *u, const Prim &P, double (*F)[SysTraits<SYS>::
 }
 
 // ---------------------------------------------------------------- speeds
-// Largest |lambda| along +-e_d for the fluid sub-system.
-// NE: |v_n| + c_s.  SR / MHD: the acoustic (fast) pair
+// Characteristic speeds of the fluid sub-system along +-e_d.
+// NE: v_n -+ c_s.  SR / MHD: the acoustic (fast) pair
 //   lambda_pm = [v_n (1 - c^2) pm c sqrt((1 - v^2)(1 - v^2 c^2 - v_n^2 (1 - c^2)))] / (1 - v^2 c^2)
-// whose larger modulus is (|v_n|(1 - c^2) + c sqrt(...)) / (1 - v^2 c^2);
-// MHD uses c^2 = v_A^2 + c_s^2 (1 - v_A^2), v_A^2 = b^2 / (rho h + b^2).
+// with c^2 = c_s^2, or for MHD c^2 = v_A^2 + c_s^2 (1 - v_A^2), v_A^2 = b^2 / (rho h + b^2).
 // (B_n, Phi) of MHD travel at the speed of light, handled by the caller.
 // gr = gamma / (gamma - 1) (rho h = rho + gr p), passed in so that the
 // per-node work holds no division.
+//
+// Both forms of c^2 are one quotient, c^2 = A / R with A = gamma p + b^2 and
+// R = rho h + b^2 (b = 0 without a field): multiplied through by R the pair is
+//   lambda_pm = [v_n (R - A) pm sqrt(A (1 - v^2) (R - v^2 A - v_n^2 (R - A)))] / (R - v^2 A),
+// one reciprocal per state instead of two (SR) or three (MHD); R - A is
+// formed without the field, in which it does not change.
+struct WaveState {
+  double A, R, R_A;  // A, R, R - A
+  double v2, uu;     // v^2, 1 - v^2
+};
+
 template <int SYS>
-DG_HD double max_speed(int d, const double *u, const Prim P, double g, double gr) {
-  const double v0 = P.v[0], v1 = P.v[1], v2s = P.v[2];
-  const double vn = (d == 0) ? v0 : ((d == 1) ? v1 : v2s);
-  if (SYS == kNE) return fabs(vn) + fast_sqrt(g * P.p * fast_rcp(P.rho));
-  const double v2 = v0 * v0 + v1 * v1 + v2s * v2s;
-  const double rhoh = P.rho + gr * P.p;
-  double c2;
-  if (SYS == kSR) {
-    c2 = g * P.p * fast_rcp(rhoh);
-  } else {
-    const double BB = sq(u[5]) + sq(u[6]) + sq(u[7]);
-    const double Bv = u[5] * v0 + u[6] * v1 + u[7] * v2s;
-    const double b2 = BB * (1.0 - v2) + Bv * Bv;
-    const double cs2 = g * P.p * fast_rcp(rhoh);
-    const double vA2 = b2 * fast_rcp(rhoh + b2);
-    c2 = vA2 + cs2 * (1.0 - vA2);
+DG_HD WaveState wave_state(const double *u, const Prim &P, double g, double gr) {
+  WaveState w;
+  w.A = g * P.p;
+  if (SYS == kNE) {
+    w.R = P.rho;
+    w.R_A = w.v2 = w.uu = 0.0;
+    return w;
   }
-  const double disc = (1.0 - v2) * (1.0 - v2 * c2 - vn * vn * (1.0 - c2));
-  return (fabs(vn) * (1.0 - c2) + fast_sqrt(c2 * disc)) * fast_rcp(1.0 - v2 * c2);
+  w.v2 = P.v[0] * P.v[0] + P.v[1] * P.v[1] + P.v[2] * P.v[2];
+  w.uu = 1.0 - w.v2;
+  w.R = P.rho + gr * P.p;
+  w.R_A = w.R - w.A;
+  if (SYS == kMHD) {
+    const double BB = sq(u[5]) + sq(u[6]) + sq(u[7]);
+    const double Bv = u[5] * P.v[0] + u[6] * P.v[1] + u[7] * P.v[2];
+    const double b2 = BB * w.uu + Bv * Bv;
+    w.A += b2;
+    w.R += b2;
+  }
+  return w;
 }
 
-// Both fluid speed bounds along +e_d, lm <= lp (the pair above; NE: v_n -+ c_s).
+// Largest modulus of the pair: (|v_n| (R - A) + sqrt(...)) / (R - v^2 A).
 template <int SYS>
-DG_HD void wave_bounds(int d, const double *u, const Prim P, double g, double gr, double &lm, double &lp) {
-  const double v0 = P.v[0], v1 = P.v[1], v2s = P.v[2];
-  const double vn = (d == 0) ? v0 : ((d == 1) ? v1 : v2s);
+DG_HD double wave_max(const WaveState &w, double vn) {
+  if (SYS == kNE) return fabs(vn) + fast_sqrt(w.A * fast_rcp(w.R));
+  const double den = w.R - w.v2 * w.A;
+  return (fabs(vn) * w.R_A + fast_sqrt(w.A * w.uu * (den - vn * vn * w.R_A))) * fast_rcp(den);
+}
+
+// Both speeds along +e_d, lm <= lp.
+template <int SYS>
+DG_HD void wave_pair(const WaveState &w, double vn, double &lm, double &lp) {
   if (SYS == kNE) {
-    const double cs = fast_sqrt(g * P.p * fast_rcp(P.rho));
+    const double cs = fast_sqrt(w.A * fast_rcp(w.R));
     lm = vn - cs;
     lp = vn + cs;
     return;
   }
-  const double v2 = v0 * v0 + v1 * v1 + v2s * v2s;
-  const double rhoh = P.rho + gr * P.p;
-  double c2;
-  if (SYS == kSR) {
-    c2 = g * P.p * fast_rcp(rhoh);
-  } else {
-    const double BB = sq(u[5]) + sq(u[6]) + sq(u[7]);
-    const double Bv = u[5] * v0 + u[6] * v1 + u[7] * v2s;
-    const double b2 = BB * (1.0 - v2) + Bv * Bv;
-    const double cs2 = g * P.p * fast_rcp(rhoh);
-    const double vA2 = b2 * fast_rcp(rhoh + b2);
-    c2 = vA2 + cs2 * (1.0 - vA2);
-  }
-  const double disc = (1.0 - v2) * (1.0 - v2 * c2 - vn * vn * (1.0 - c2));
-  const double r = fast_rcp(1.0 - v2 * c2);
-  const double a = vn * (1.0 - c2), b = fast_sqrt(c2 * disc);
+  const double den = w.R - w.v2 * w.A, r = fast_rcp(den);
+  const double a = vn * w.R_A, b = fast_sqrt(w.A * w.uu * (den - vn * vn * w.R_A));
   lm = (a - b) * r;
   lp = (a + b) * r;
+}
+
+template <int SYS>
+DG_HD double max_speed(int d, const double *u, const Prim P, double g, double gr) {
+  const double v0 = P.v[0], v1 = P.v[1], v2s = P.v[2];
+  return wave_max<SYS>(wave_state<SYS>(u, P, g, gr), (d == 0) ? v0 : ((d == 1) ? v1 : v2s));
+}
+
+template <int SYS>
+DG_HD void wave_bounds(int d, const double *u, const Prim P, double g, double gr, double &lm, double &lp) {
+  const double v0 = P.v[0], v1 = P.v[1], v2s = P.v[2];
+  wave_pair<SYS>(wave_state<SYS>(u, P, g, gr), (d == 0) ? v0 : ((d == 1) ? v1 : v2s), lm, lp);
 }
 
 // Roe dissipation for the Newtonian ideal gas (eq. Roe): D = sum_i |lambda_i|
@@ -457,6 +472,29 @@ DG_HD Prim prims_at_pressure(const double *u, double g, double p, bool poly = fa
   P.v[2] = u[3] * iz;
   P.rho = u[0] * (fast_sqrt((z - Sabs) * (z + Sabs)) * iz);
   P.p = p;
+  return P;
+}
+
+// SR: velocity and wave quantities of a state whose pressure is known, for
+// callers that need no density: with q = z^2 - S^2 = (z - |S|)(z + |S|),
+// 1 - v^2 = q / z^2 and rho h = q / z, so that the square root in rho is not
+// taken.
+DG_HD Prim sr_wave_state(const double *u, double p, double g, WaveState &w) {
+  Prim P;
+  const double S2 = u[1] * u[1] + u[2] * u[2] + u[3] * u[3];
+  const double Sabs = fast_sqrt(S2);
+  const double z = u[4] + u[0] + p;
+  const double iz = fast_rcp(z);
+  P.v[0] = u[1] * iz;
+  P.v[1] = u[2] * iz;
+  P.v[2] = u[3] * iz;
+  P.p = p;
+  w.R = (z - Sabs) * (z + Sabs) * iz;
+  w.A = g * p;
+  w.R_A = w.R - w.A;
+  w.v2 = S2 * iz * iz;
+  w.uu = w.R * iz;
+  P.rho = 0.0;  // not formed
   return P;
 }
 

@@ -154,6 +154,11 @@ __device__ __forceinline__ void load_node(const double *U, const double *Pr, int
   }
 }
 
+// Tables that no kernel writes, read at wave-uniform addresses through the
+// scalar cache.
+typedef __attribute__((address_space(4))) const int64_t scalar_i64;
+typedef __attribute__((address_space(4))) const int32_t scalar_i32;
+
 // The work of one workgroup on element group grp, with BT threads and the
 // LDS block smem (the kernels below choose grp and provide both).
 template <int SYS, int N, int STAGE, int EPB_, bool MIXED, int BT, int FLUX = kLLF, bool MOM = false>
@@ -185,6 +190,14 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
   }
   const int ci = a % NP, cj = (a / NP) % NP, ck = a / NF;
   const int64_t nn = A.nnodes;
+  // A workgroup of a uniform mesh owns consecutive nodes: its rows start at
+  // scalar addresses and a lane adds its thread index (elements of a mixed
+  // list are anywhere).
+  constexpr bool kRun = !MIXED;
+  const int64_t q0 = (int64_t)grp * EPB * NPE;
+  auto own_row = [&](auto *rows, int k) { return rows + (kRun ? k * nn + q0 : k * nn); };
+  using OQ = std::conditional_t<kRun, uint32_t, int64_t>;
+  const OQ oq = kRun ? (OQ)tid : (OQ)q;
 
   // ---- face tasks.  Task t (padded per direction to whole waves) belongs to
   // direction d = t / TPDP; within it, element slot fle, side and face node fn.
@@ -192,6 +205,57 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
   // (kind 2) or, on mixed meshes, the mortar kernel's lift terms (kind 3).
   auto decode = [&](auto dc, int r, int &fle, int &f, int &fn, int &ai, int &kind, int64_t &src) {
     constexpr int d = decltype(dc)::value;
+    if constexpr (EPB == 1) {
+      // One element per workgroup: its two neighbours along d are the same
+      // for every lane, so they are found on the scalar unit (index
+      // arithmetic or two adjacent table entries) and a lane only picks its
+      // side.  (Found per lane it took half of the operator's integer
+      // instructions, twice per task: 173 per wave, 110 now.)
+      const bool side = r >= NF;
+      fle = 0;
+      fn = side ? r - NF : r;
+      f = 2 * d + (side ? 1 : 0);
+      const int tb = fn / NP, ta = fn - NP * tb;
+      const int base = d == 0 ? NP * (ta + NP * tb) : (d == 1 ? ta + NF * tb : ta + NP * tb);
+      constexpr int st = d == 0 ? 1 : (d == 1 ? NP : NF);
+      ai = base + (side ? N * st : 0);
+      const int an = base + (side ? 0 : N * st);
+      if constexpr (MIXED) {
+        scalar_i64 *xs = (scalar_i64 *)(A.mtab + 7 * (int64_t)grp + 1 + 2 * d);
+        const int64_t x0 = xs[0], x1 = xs[1];
+        const int64_t x = side ? x1 : x0;
+        kind = x < 0 ? 3 : 1;
+        src = x < 0 ? -1 - x + fn : x + an;
+        return;
+      }
+      if (A.periodic) {
+        const uint32_t e = (uint32_t)grp;
+        const uint32_t q1 = fastdiv(e, A.div_nx);
+        uint32_t nd, es, c;
+        if constexpr (d == 0) {
+          nd = (uint32_t)A.nx;
+          es = 1;
+          c = e - q1 * nd;
+        } else {
+          const uint32_t q2 = fastdiv(q1, A.div_ny);
+          nd = (uint32_t)(d == 1 ? A.ny : A.nz);
+          es = d == 1 ? (uint32_t)A.nx : (uint32_t)A.nx * (uint32_t)A.ny;
+          c = d == 1 ? q1 - q2 * nd : q2;
+        }
+        const uint32_t wrap = (nd - 1) * es;
+        const int64_t x0 = (int64_t)(c == 0 ? e + wrap : e - es) * NPE;
+        const int64_t x1 = (int64_t)(c == nd - 1 ? e - wrap : e + es) * NPE;
+        kind = 1;
+        src = (side ? x1 : x0) + an;
+        return;
+      }
+      scalar_i32 *nb = (scalar_i32 *)(A.nbr + 6 * (int64_t)grp + 2 * d);
+      const int32_t n0 = nb[0], n1 = nb[1];
+      const int32_t en = side ? n1 : n0;
+      kind = en < 0 ? 2 : 1;
+      src = en < 0 ? ((side ? A.boff[2 * d + 1] : A.boff[2 * d]) + (int64_t)(-1 - en) * NF + fn) * 16 : (int64_t)en * NPE + an;
+      return;
+    }
     fle = r / (2 * NF);
     const int r2 = r - fle * 2 * NF;
     const int side = r2 / NF;
@@ -245,17 +309,40 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
     kind = 1;
     src = en * NPE + an;
   };
-  // raw exterior values of a mesh node: U and the primitive rows it carries
-  auto load_raw = [&](int64_t qe, double *ue, double *pr) {
+  // raw values of a node, U and the primitive rows it carries: mesh node
+  // `src` (kind 1) or row `src` of the boundary buffer (kind 2)
+  auto load_raw = [&](int kind, int64_t src, double *ue, double *pr) {
+    if (MIXED || A.periodic) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) ue[v] = A.U[v * nn + qe];
-    if (SYS == kSR) pr[0] = A.P[4 * nn + qe];
-    if (SYS == kMHD) {
+      for (int v = 0; v < NV; ++v) ue[v] = A.U[v * nn + src];
+      if (SYS == kSR) pr[0] = A.P[4 * nn + src];
+      if (SYS == kMHD) {
 #pragma unroll
-      for (int k = 0; k < 5; ++k) pr[k] = A.P[k * nn + qe];
+        for (int k = 0; k < 5; ++k) pr[k] = A.P[k * nn + src];
+      }
+    } else {
+      const bool bnd = kind == 2;
+      const double *pu = (bnd ? A.bface : A.U) + src, *pp = bnd ? A.bface + src + 9 : A.P + src;
+      const int64_t st = bnd ? 1 : nn;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) ue[v] = pu[v * st];
+      if (SYS == kSR) pr[0] = pp[4 * st];
+      if (SYS == kMHD) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k) pr[k] = pp[k * st];
+      }
     }
   };
   constexpr int NPRX = C::NPR > 0 ? C::NPR : 1;
+  // primitives (SR: velocity and pressure; MHD: given) and wave quantities
+  auto state_waves = [&](const double *u, double p, Prim &P, WaveState &w) {
+    if constexpr (SYS == kSR) {
+      P = sr_wave_state(u, p, A.gamma, w);
+    } else {
+      if constexpr (SYS == kNE) P = prims_at_pressure<kNE>(u, A.gamma, 0.0, A.poly);
+      w = wave_state<SYS>(u, P, A.gamma, A.gratio);
+    }
+  };
   // one face task: F*.n - F_int.n into the face slot (pre: the exterior
   // state was loaded at the start of the kernel)
   auto face_task = [&](auto dc, auto prec, int r, const double *ue_pre, const double *pr_pre) {
@@ -288,24 +375,20 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
         Pi.v[1] = own[(NV + 2) * NPE];
         Pi.v[2] = own[(NV + 3) * NPE];
         Pi.p = own[(NV + 4) * NPE];
-      } else {
-        Pi = prims_at_pressure<SYS>(ui, A.gamma, SYS == kSR ? own[NV * NPE] : 0.0, A.poly);
       }
+      WaveState wi;
+      state_waves(ui, SYS == kSR ? own[NV * NPE] : 0.0, Pi, wi);
       flux_normal<SYS>(d, ui, Pi, Fi);
 #pragma unroll
       for (int v = 0; v < NV; ++v) slot[v * 6 * NF] = Fi[v];
-      if constexpr (FLUX == kHLL) wave_bounds<SYS>(d, ui, Pi, A.gamma, A.gratio, lmi, lpi);
-      else if constexpr (FLUX == kLLF) si = max_speed<SYS>(d, ui, Pi, A.gamma, A.gratio);
+      if constexpr (FLUX == kHLL) wave_pair<SYS>(wi, Pi.v[d], lmi, lpi);
+      else if constexpr (FLUX == kLLF) si = wave_max<SYS>(wi, Pi.v[d]);
     }
     // the exterior state
     double ue[NV], Fe[NV];
     Prim Pe;
-    if (kind == 2) {
-      const double *bs = A.bface + src;
-#pragma unroll
-      for (int v = 0; v < NV; ++v) ue[v] = bs[v];
-      Pe.rho = bs[9]; Pe.v[0] = bs[10]; Pe.v[1] = bs[11]; Pe.v[2] = bs[12]; Pe.p = bs[13];
-    } else {
+    WaveState we;
+    {
       double pr[NPRX];
       if constexpr (pre) {
 #pragma unroll
@@ -313,13 +396,12 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
 #pragma unroll
         for (int k = 0; k < NPRX; ++k) pr[k] = pr_pre[k];
       } else {
-        load_raw(src, ue, pr);
+        load_raw(kind, src, ue, pr);
       }
       if (SYS == kMHD) {
         Pe.rho = pr[0]; Pe.v[0] = pr[1]; Pe.v[1] = pr[2]; Pe.v[2] = pr[3]; Pe.p = pr[4];
-      } else {
-        Pe = prims_at_pressure<SYS>(ue, A.gamma, SYS == kSR ? pr[0] : 0.0, A.poly);
       }
+      state_waves(ue, SYS == kSR ? pr[0] : 0.0, Pe, we);
     }
     flux_normal<SYS>(d, ue, Pe, Fe);
     if constexpr ((FLUX == kMarquina || FLUX == kRoe) && SYS == kNE) {
@@ -349,7 +431,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
       // c = -s- / (s+ - s-), the bounds (largest and smallest speed along the
       // outward normal of either side) clipped by zero
       double lm, lp;
-      wave_bounds<SYS>(d, ue, Pe, A.gamma, A.gratio, lm, lp);
+      wave_pair<SYS>(we, Pe.v[d], lm, lp);
       const double sp = fmax(0.0, side ? fmax(lpi, lp) : -fmin(lmi, lm));
       const double sm = fmin(0.0, side ? fmin(lmi, lm) : -fmax(lpi, lp));
       const double cf = -sm * fast_rcp(sp - sm);
@@ -364,7 +446,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
       }
       return;
     }
-    const double alpha = fmax(si, max_speed<SYS>(d, ue, Pe, A.gamma, A.gratio));
+    const double alpha = fmax(si, wave_max<SYS>(we, Pe.v[d]));
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       double al = alpha;
@@ -392,7 +474,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
     if (d0 == 0) decode(std::integral_constant<int, 0>{}, r0, fle, f, fn, ai, kind, src);
     else if (d0 == 1) decode(std::integral_constant<int, 1>{}, r0, fle, f, fn, ai, kind, src);
     else decode(std::integral_constant<int, 2>{}, r0, fle, f, fn, ai, kind, src);
-    if (kind == 1) load_raw(src, ue0, pr0);
+    if (kind == 1 || kind == 2) load_raw(kind, src, ue0, pr0);
   }
   double *mybuf = svol + le * RS * NPE;  // [row][node] for this element
   double *myslot = sslot + le * NV * 6 * NF;
@@ -400,7 +482,10 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
   // volume buffer, for the face phase
   if (active) {
     double ur[NV], prr[NPRX];
-    load_raw(q, ur, prr);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) ur[v] = own_row(A.U, v)[oq];
+#pragma unroll
+    for (int k = 0; k < C::NPR; ++k) prr[k] = own_row(A.P, SYS == kSR ? 4 : k)[oq];
 #pragma unroll
     for (int v = 0; v < NV; ++v) mybuf[v * NPE + a] = ur[v];
 #pragma unroll
@@ -508,7 +593,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
     // dU/dt is streamed past L2 (no element group reads it), which leaves
     // L2 to the neighbour states the next groups read across their faces
 #pragma unroll
-    for (int v = 0; v < NV; ++v) __builtin_nontemporal_store(acc[v], &A.out[v * nn + q]);
+    for (int v = 0; v < NV; ++v) __builtin_nontemporal_store(acc[v], own_row(A.out, v) + oq);
     return;
   }
   // ---- Shu-Osher combination and tail recovery
@@ -574,8 +659,13 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
 
 // Uniform mesh (or one degree of a mixed mesh): one launch, EPB elements
 // per workgroup, one thread per volume node.
-// (SR hydro: six waves per SIMD, 80 VGPRs, at the cost of a few spilled
-// registers: 4% faster than the five waves its 84 registers allow)
+// The operator on 32^3 elements of degree 4 (SR): 552 vector instructions per
+// wave and 68 VGPRs (7 waves per SIMD), 111 us at 4.1 TB/s of counted traffic,
+// of the 4.6 TB/s a large copy reaches here; with the neighbours found per
+// lane and the wave speeds from three square roots and three reciprocals per
+// state, 704 instructions, 80 VGPRs and four spilled registers, 122 us.
+// (SR hydro is held to six waves per SIMD: its limited stage would take more
+// than 80 VGPRs, which was slower.)
 template <int SYS, int N, int STAGE, int EPB_ = default_epb<SYS, N>(), bool MIXED = false, int FLUX = kLLF,
           bool MOM = false>
 __global__ void __launch_bounds__((RhsCfg<SYS, N, EPB_>::THREADS)) __attribute__((amdgpu_waves_per_eu(SYS == kSR ? 6 : 1)))

@@ -1,0 +1,81 @@
+"""The element kernel's neighbour finding and exterior states on small and
+lopsided boxes: one element per direction (an element its own neighbour),
+two (both neighbours the same element), odd counts, and box faces with fixed
+exterior states in one direction, for one element per workgroup and for
+several.
+
+Bar: the operator within 1e-12 norm-wise per variable of the oracle, the
+operator's overall scale as floor (a variable that stays ~0 carries only the
+rounding of fluxes of that scale)."""
+import numpy as np
+import pytest
+
+from paper_1609_00098_amd import synth
+from tests.gpu_util import normwise_err, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+NE, SR, MHD = 0, 1, 2
+GAMMA = {NE: 5.0 / 3.0, SR: 4.0 / 3.0, MHD: 4.0 / 3.0}
+LO, HI = (-0.2, 0.1, 0.0), (0.8, 1.3, 0.7)
+
+
+@pytest.fixture(scope="module")
+def dg():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1609_00098_amd import dgmi
+    return dgmi
+
+
+def _state(ora, system, m, seed):
+    xyz = ora.node_coords(m)
+    unit = (xyz - np.array(LO)[:, None]) / (np.array(HI) - np.array(LO))[:, None]
+    prim = synth.fourier_random_prims(unit, seed=seed, w_max=3.0, rho_range=(0.5, 2.0), p_range=(0.1, 10.0))
+    rng = np.random.default_rng(seed)
+    # the two sides of every face differ
+    prim[[0, 4]] *= 1.0 + 0.02 * rng.uniform(-1.0, 1.0, (2, prim.shape[1]))
+    mag = None
+    if system == MHD:
+        mag = 0.3 * np.stack([np.sin(2 * np.pi * (rng.integers(1, 3, size=3) @ unit) + c) for c in range(4)])
+        mag[0] += 1.0
+    return ora.prim2cons(system, GAMMA[system], prim, mag), prim
+
+
+# degrees with one element per workgroup (NE and SR from 4, SRMHD 3 and from 5)
+# and with several
+CASES = [(NE, 2), (NE, 4), (NE, 6), (SR, 3), (SR, 4), (SR, 7), (MHD, 3), (MHD, 4), (MHD, 6)]
+
+
+@pytest.mark.parametrize("nel", [(1, 1, 1), (2, 1, 3), (5, 3, 2)])
+@pytest.mark.parametrize("system,N", CASES)
+@pytest.mark.parametrize("flux", ["llf", "hll"])
+def test_operator_small_boxes(ora, dg, system, N, nel, flux):
+    g = GAMMA[system]
+    m = ora.mesh(system, nel, N, g, lo=LO, hi=HI, kappa=0.5, flux=flux)
+    G = dg.Mesh(system, nel, N, g, lo=LO, hi=HI, kappa=0.5, flags=dg.FLAG_HLL if flux == "hll" else 0)
+    U, prim = _state(ora, system, m, seed=10 * N + system)
+    dUo, Po, nf = ora.rhs(m, U)
+    assert nf == 0
+    P, dU = to_dev(prim * (1 + 1e-3)), G.empty_state()
+    dg.dg_rhs(G, to_dev(U), P, dU)
+    assert dg.dgmi_failures(G) == 0
+    assert np.all(normwise_err(to_host(P), Po) <= 1e-12)
+    assert np.all(normwise_err(to_host(dU), dUo, floor_scale=np.abs(dUo).max()) <= 1e-12)
+
+
+@pytest.mark.parametrize("direction", [0, 1, 2])
+@pytest.mark.parametrize("system,N", CASES)
+def test_operator_fixed_faces_one_direction(ora, dg, system, N, direction):
+    g, nel = GAMMA[system], (3, 2, 2)
+    lo, hi = [1.0, 0.1, -0.2, 0.05, 1.0], [0.7, -0.1, 0.3, 0.2, 2.0]
+    if system == MHD:
+        lo, hi = lo + [0.5, 0.2, -0.1, 0.03], hi + [0.4, -0.2, 0.3, -0.05]
+    m = ora.mesh(system, nel, N, g, lo=LO, hi=HI, kappa=0.5, bc={direction: (tuple(lo), tuple(hi))})
+    G = dg.Mesh(system, nel, N, g, lo=LO, hi=HI, kappa=0.5)
+    dg.dgmi_set_boundary(G, direction, lo, hi)
+    U, prim = _state(ora, system, m, seed=7 + N)
+    dUo, _, nf = ora.rhs(m, U)
+    assert nf == 0
+    dU = G.empty_state()
+    dg.dg_rhs(G, to_dev(U), to_dev(prim * (1 + 1e-3)), dU)
+    assert np.all(normwise_err(to_host(dU), dUo, floor_scale=np.abs(dUo).max()) <= 1e-12)
