@@ -422,6 +422,13 @@ static dgmi_status mixed_setup(dgmi_ctx *c, const std::vector<double> &hx, hipSt
   return DGMI_OK;
 }
 
+// Whether an RK stage streams U^n and its output past the caches: its arrays
+// (U, U^n and the output, pressures in and out) exceed the 256 MiB last-level
+// cache, so that the next stage would not find them there anyway.
+static int stage_streams(const dgmi_ctx *c) {
+  return 8 * (int64_t)(3 * c->nv + 2) * c->nnodes > ((int64_t)256 << 20);
+}
+
 static dgmi::RhsArgs mix_args(dgmi_ctx *c, int N) {
   dgmi::RhsArgs a{};
   a.elist = c->d_elist + c->lstart[N];
@@ -442,6 +449,7 @@ static dgmi::RhsArgs mix_args(dgmi_ctx *c, int N) {
   a.nx = c->nx;
   a.ny = c->ny;
   a.nz = c->nz;
+  a.streamed = stage_streams(c);
   return a;
 }
 
@@ -877,6 +885,7 @@ static dgmi::RhsArgs rhs_args(dgmi_ctx *c) {
   a.nx = c->nx;
   a.ny = c->ny;
   a.nz = c->nz;
+  a.streamed = stage_streams(c);
   return a;
 }
 

@@ -52,6 +52,8 @@ struct RhsArgs {
   double inv_wend;     // 1/w_0 = N(N+1)/2
   double a, b, dt;     // Shu-Osher stage: out = a Un + b (U + dt L(U))
   int nx, ny, nz;      // elements per direction
+  int streamed;        // stage kernel: U^n is read and the output written past the caches (set where a stage's
+                       // arrays exceed the last-level cache)
   int full_prims;      // stage kernel: write all five primitive rows (else NE/SR write only p)
   const double *dtp;   // stage kernel: if set, dt is read from this device scalar
   // mixed degrees: the launch of degree N processes the nlist elements in
