@@ -205,7 +205,7 @@ struct dgmi_ctx {
   double vortex[6] = {0};         // isentropic vortex parameters
   double *d_bface = nullptr;      // analytic exterior states per boundary face node
   int64_t boff[7] = {0};
-  double hbc[6 * 16] = {0};       // per box face: conserved [0, nv), primitives [9, 14)
+  double hbc[6 * 16] = {0};       // per box face: conserved [0, nv), primitives [9, 14), SRMHD z at 14
   double *d_bc = nullptr;         // device copy
   // slope limiter (uniform meshes)
   int lim_kind = 0;               // DGMI_LIMITER_*
@@ -1060,6 +1060,7 @@ static dgmi_status step_impl(dgmi_ctx *ctx, double *U, double *prim_inout, doubl
   // stage 1: U1 = U + dt L(U)
   a.U = U; a.P = prim_inout; a.a = 0.0; a.b = 1.0;
   if ((st = stage(b.U1, b.P1, t0)) != DGMI_OK) return st;
+  a.in_pz = ctx->sys == 2 && !limit;
   // stage 2: U2 = 3/4 U + 1/4 (U1 + dt L(U1))
   a.U = b.U1; a.P = b.P1; a.a = 0.75; a.b = 0.25;
   if ((st = stage(b.U2, b.P2, t0 + dt)) != DGMI_OK) return st;
@@ -1152,6 +1153,7 @@ dgmi_status dgmi_set_boundary(dgmi_ctx *ctx, int32_t direction, const double *st
         default: dgmi::prim_to_cons<dgmi::kMHD>(P, st + 5, ctx->gamma, row); break;
       }
       row[9] = P.rho; row[10] = P.v[0]; row[11] = P.v[1]; row[12] = P.v[2]; row[13] = P.p;
+      if (ctx->sys == 2) row[14] = (P.rho + ctx->gamma / (ctx->gamma - 1.0) * P.p) / (1.0 - v2);  // z = rho h W^2
     }
     bc = 1;
   }

@@ -498,8 +498,36 @@ DG_HD Prim sr_wave_state(const double *u, double p, double g, WaveState &w) {
   return P;
 }
 
+// SRMHD: velocity and wave quantities of a state whose pressure and
+// z = rho h W^2 are known, without the density: with T = S.B,
+// v = (S + (T / z) B) / (z + B^2) (the recovery's own closing formula),
+// B.v = T / z and rho h = z (1 - v^2).
+DG_HD Prim mhd_wave_state(const double *u, double p, double z, double g, WaveState &w) {
+  Prim P;
+  const double BB = u[5] * u[5] + u[6] * u[6] + u[7] * u[7];
+  const double T = u[1] * u[5] + u[2] * u[6] + u[3] * u[7];
+  const double em = z + BB;
+  const double r = fast_rcp(z * em);
+  const bool rest = z < 0.0;  // a failed recovery's state at rest, z = -rho h
+  const double Bv = rest ? 0.0 : T * (em * r), iem = rest ? 0.0 : z * r;
+  P.v[0] = (u[1] + Bv * u[5]) * iem;
+  P.v[1] = (u[2] + Bv * u[6]) * iem;
+  P.v[2] = (u[3] + Bv * u[7]) * iem;
+  P.p = p;
+  P.rho = 0.0;  // not formed
+  w.v2 = P.v[0] * P.v[0] + P.v[1] * P.v[1] + P.v[2] * P.v[2];
+  w.uu = 1.0 - w.v2;
+  const double rhoh = rest ? -z : z * w.uu, b2 = BB * w.uu + Bv * Bv;
+  w.A = g * p;
+  w.R_A = rhoh - w.A;
+  w.A += b2;
+  w.R = rhoh + b2;
+  return P;
+}
+
 struct C2PResult {
   Prim P;
+  double z;  // MHD: rho h W^2 at the final pressure, or -rho h of the state at rest returned on failure
   int iters;
   int ok;
 };
@@ -645,7 +673,10 @@ DG_HD C2PResult recover(const double *u, double g, double p0, double tol, int ma
   R.P.rho = D;
   R.P.v[0] = R.P.v[1] = R.P.v[2] = 0.0;
   R.P.p = hi;
-  if (!(D > 0.0) || !(hi > 0.0) || !(E > 0.0)) return R;
+  if (!(D > 0.0) || !(hi > 0.0) || !(E > 0.0)) {
+    if (SYS == kMHD) R.z = -(D + g / gm1 * hi);
+    return R;
+  }
   if (SYS == kSR && !(E * E - S2 > D * D)) return R;  // f(0) <= 0: no physical state
   const double Sabs = fast_sqrt(S2);
   double p = (p0 > lo && p0 < hi) ? p0 : hi;
@@ -783,6 +814,7 @@ DG_HD C2PResult recover(const double *u, double g, double p0, double tol, int ma
     const double x0 = (em_prev > 0.0) ? fmax(em_prev + (e - e_prev), 2.0 * e / 3.0 + 1e-3 * e) : e;
     em = cubic_top_root(e, dcub, fmin(x0, e));
     z = em - BB;
+    R.z = z;
     const double Tz = T * fast_rcp(z), iem = fast_rcp(em);
     R.P.v[0] = (S0 + Tz * u[5]) * iem;
     R.P.v[1] = (S1 + Tz * u[6]) * iem;

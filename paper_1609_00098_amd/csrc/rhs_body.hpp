@@ -98,14 +98,18 @@ __device__ __forceinline__ int brick_map(int seq, const BrickMap &m) {
 }
 
 // Elements per workgroup of the uniform kernels (measured: one element at
-// degree 4 for NE / SR and at degree 3 for SRMHD ran 1-2% faster than two,
-// four was slower).
+// degree 4 for NE / SR ran 1-2% faster than two, four was slower; SRMHD at
+// degree 3 with two, whose face tasks fill three waves, 3.97 ms a step of 64^3
+// elements against 4.32 ms with one, 5.4 with three and 5.0 with four).
 template <int SYS, int N>
 constexpr int default_epb() {
-  return (N == 1) ? 8 : (N == 2) ? 9 : (N == 3) ? (SYS == kMHD ? 1 : 4) : (N == 4) ? (SYS == kMHD ? 2 : 1) : 1;
+  return (N == 1) ? 8 : (N == 2) ? 9 : (N == 3) ? (SYS == kMHD ? 2 : 4) : (N == 4) ? (SYS == kMHD ? 2 : 1) : 1;
 }
 
-template <int SYS, int N, int EPB_ = default_epb<SYS, N>(), int FLUX = kLLF>
+// PZ (SRMHD stages of dg_step after the first, see launch_one): the input's
+// primitive rows are 4, the pressure, and 0, z = rho h W^2, from which and U
+// the rest follows in closed form, instead of all five.
+template <int SYS, int N, int EPB_ = default_epb<SYS, N>(), int FLUX = kLLF, bool PZ = false>
 struct RhsCfg {
   static constexpr int NP = N + 1;
   static constexpr int NPE = NP * NP * NP;
@@ -124,8 +128,8 @@ struct RhsCfg {
   static constexpr int WORK = (SYS == kMHD && 3 * TPDP > EPB * NPE) ? 3 * TPDP : EPB * NPE;
   static constexpr int THREADS = ((WORK + 63) / 64) * 64;
   // primitive rows a node's state carries into the face phase: NE none (they
-  // follow from U), SR the pressure, SRMHD all five
-  static constexpr int NPR = SYS == kSR ? 1 : (SYS == kMHD ? 5 : 0);
+  // follow from U), SR the pressure, SRMHD all five or (PZ) pressure and z
+  static constexpr int NPR = SYS == kSR ? 1 : (SYS == kMHD ? (PZ ? 2 : 5) : 0);
   static constexpr int RS = NV + NPR;  // rows per element in the volume buffer
   // LDS (doubles): the volume buffer [EPB][RS][NPE] (one direction's nodal
   // fluxes, then each node's state for the face phase), face slots
@@ -161,9 +165,10 @@ typedef __attribute__((address_space(4))) const int32_t scalar_i32;
 
 // The work of one workgroup on element group grp, with BT threads and the
 // LDS block smem (the kernels below choose grp and provide both).
-template <int SYS, int N, int STAGE, int EPB_, bool MIXED, int BT, int FLUX = kLLF, bool MOM = false>
+template <int SYS, int N, int STAGE, int EPB_, bool MIXED, int BT, int FLUX = kLLF, bool MOM = false, bool PZ = false>
 __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem) {
-  using C = RhsCfg<SYS, N, EPB_, FLUX>;
+  using C = RhsCfg<SYS, N, EPB_, FLUX, PZ>;
+  static_assert(!PZ || (SYS == kMHD && STAGE == 1 && !MIXED && !MOM), "PZ: uniform SRMHD stages");
   static_assert(BT >= (N + 1) * (N + 1), "one thread per entry of D");
   constexpr int NP = C::NP, NPE = C::NPE, NF = C::NF, NV = C::NV, EPB = C::EPB, RS = C::RS;
   double *svol = smem;
@@ -205,55 +210,66 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
   // (kind 2) or, on mixed meshes, the mortar kernel's lift terms (kind 3).
   auto decode = [&](auto dc, int r, int &fle, int &f, int &fn, int &ai, int &kind, int64_t &src) {
     constexpr int d = decltype(dc)::value;
-    if constexpr (EPB == 1) {
-      // One element per workgroup: its two neighbours along d are the same
-      // for every lane, so they are found on the scalar unit (index
-      // arithmetic or two adjacent table entries) and a lane only picks its
-      // side.  (Found per lane it took half of the operator's integer
-      // instructions, twice per task: 173 per wave, 110 now.)
-      const bool side = r >= NF;
-      fle = 0;
-      fn = side ? r - NF : r;
+    if constexpr (EPB <= 2) {
+      // One or two elements per workgroup: their neighbours along d are the
+      // same for every lane, so they are found on the scalar unit (index
+      // arithmetic or adjacent table entries) and a lane only picks its
+      // element and side.  (Found per lane it took half of the operator's
+      // integer instructions at EPB = 1, twice per task: 173 per wave, 110 now.)
+      fle = EPB == 1 || r < 2 * NF ? 0 : 1;
+      const int r2 = EPB == 1 ? r : r - 2 * NF * fle;
+      const bool side = r2 >= NF;
+      fn = side ? r2 - NF : r2;
       f = 2 * d + (side ? 1 : 0);
+      kind = 0;
+      const int64_t cnt = MIXED ? A.nlist : A.nelem;
+      if (EPB == 2 && (int64_t)grp * EPB + fle >= cnt) return;
       const int tb = fn / NP, ta = fn - NP * tb;
       const int base = d == 0 ? NP * (ta + NP * tb) : (d == 1 ? ta + NF * tb : ta + NP * tb);
       constexpr int st = d == 0 ? 1 : (d == 1 ? NP : NF);
       ai = base + (side ? N * st : 0);
       const int an = base + (side ? 0 : N * st);
+      // the workgroup's last slot, or the one before where the list ends early
+      const int64_t s0 = (int64_t)grp * EPB, s1 = s0 + EPB - 1 < cnt ? s0 + EPB - 1 : cnt - 1;
       if constexpr (MIXED) {
-        scalar_i64 *xs = (scalar_i64 *)(A.mtab + 7 * (int64_t)grp + 1 + 2 * d);
-        const int64_t x0 = xs[0], x1 = xs[1];
-        const int64_t x = side ? x1 : x0;
+        scalar_i64 *p0 = (scalar_i64 *)(A.mtab + 7 * s0 + 1 + 2 * d), *p1 = (scalar_i64 *)(A.mtab + 7 * s1 + 1 + 2 * d);
+        const int64_t l0 = p0[0], h0 = p0[1], l1 = p1[0], h1 = p1[1];
+        const int64_t x = fle == 0 ? (side ? h0 : l0) : (side ? h1 : l1);
         kind = x < 0 ? 3 : 1;
         src = x < 0 ? -1 - x + fn : x + an;
         return;
       }
       if (A.periodic) {
-        const uint32_t e = (uint32_t)grp;
-        const uint32_t q1 = fastdiv(e, A.div_nx);
-        uint32_t nd, es, c;
-        if constexpr (d == 0) {
-          nd = (uint32_t)A.nx;
-          es = 1;
-          c = e - q1 * nd;
-        } else {
-          const uint32_t q2 = fastdiv(q1, A.div_ny);
-          nd = (uint32_t)(d == 1 ? A.ny : A.nz);
-          es = d == 1 ? (uint32_t)A.nx : (uint32_t)A.nx * (uint32_t)A.ny;
-          c = d == 1 ? q1 - q2 * nd : q2;
-        }
+        const uint32_t nd = (uint32_t)(d == 0 ? A.nx : (d == 1 ? A.ny : A.nz));
+        const uint32_t es = d == 0 ? 1u : (d == 1 ? (uint32_t)A.nx : (uint32_t)A.nx * (uint32_t)A.ny);
         const uint32_t wrap = (nd - 1) * es;
-        const int64_t x0 = (int64_t)(c == 0 ? e + wrap : e - es) * NPE;
-        const int64_t x1 = (int64_t)(c == nd - 1 ? e - wrap : e + es) * NPE;
+        uint32_t lo[2], hi[2];
+#pragma unroll
+        for (int k = 0; k < EPB; ++k) {
+          const uint32_t e = (uint32_t)(s0 + k);
+          const uint32_t q1 = fastdiv(e, A.div_nx);
+          uint32_t c;
+          if constexpr (d == 0) {
+            c = e - q1 * nd;
+          } else {
+            const uint32_t q2 = fastdiv(q1, A.div_ny);
+            c = d == 1 ? q1 - q2 * nd : q2;
+          }
+          lo[k] = c == 0 ? e + wrap : e - es;
+          hi[k] = c == nd - 1 ? e - wrap : e + es;
+        }
+        const uint32_t e0 = side ? hi[0] : lo[0];
+        const uint32_t en = EPB == 1 || fle == 0 ? e0 : (side ? hi[EPB - 1] : lo[EPB - 1]);
         kind = 1;
-        src = (side ? x1 : x0) + an;
+        src = (int64_t)en * NPE + an;
         return;
       }
-      scalar_i32 *nb = (scalar_i32 *)(A.nbr + 6 * (int64_t)grp + 2 * d);
-      const int32_t n0 = nb[0], n1 = nb[1];
-      const int32_t en = side ? n1 : n0;
+      scalar_i32 *b0 = (scalar_i32 *)(A.nbr + 6 * s0 + 2 * d), *b1 = (scalar_i32 *)(A.nbr + 6 * s1 + 2 * d);
+      const int32_t l0 = b0[0], h0 = b0[1], l1 = b1[0], h1 = b1[1];
+      const int32_t en = fle == 0 ? (side ? h0 : l0) : (side ? h1 : l1);
       kind = en < 0 ? 2 : 1;
-      src = en < 0 ? ((side ? A.boff[2 * d + 1] : A.boff[2 * d]) + (int64_t)(-1 - en) * NF + fn) * 16 : (int64_t)en * NPE + an;
+      src = en < 0 ? ((side ? A.boff[2 * d + 1] : A.boff[2 * d]) + (int64_t)(-1 - en) * NF + fn) * 16
+                   : (int64_t)en * NPE + an;
       return;
     }
     fle = r / (2 * NF);
@@ -311,35 +327,38 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
   };
   // raw values of a node, U and the primitive rows it carries: mesh node
   // `src` (kind 1) or row `src` of the boundary buffer (kind 2)
+  auto prow = [](int k) { return SYS == kSR ? 4 : (PZ ? 4 - 4 * k : k); };  // the k-th carried row
   auto load_raw = [&](int kind, int64_t src, double *ue, double *pr) {
     if (MIXED || A.periodic) {
 #pragma unroll
       for (int v = 0; v < NV; ++v) ue[v] = A.U[v * nn + src];
-      if (SYS == kSR) pr[0] = A.P[4 * nn + src];
-      if (SYS == kMHD) {
 #pragma unroll
-        for (int k = 0; k < 5; ++k) pr[k] = A.P[k * nn + src];
-      }
+      for (int k = 0; k < C::NPR; ++k) pr[k] = A.P[prow(k) * nn + src];
     } else {
       const bool bnd = kind == 2;
       const double *pu = (bnd ? A.bface : A.U) + src, *pp = bnd ? A.bface + src + 9 : A.P + src;
       const int64_t st = bnd ? 1 : nn;
 #pragma unroll
       for (int v = 0; v < NV; ++v) ue[v] = pu[v * st];
-      if (SYS == kSR) pr[0] = pp[4 * st];
-      if (SYS == kMHD) {
+      // (z of a box-face state is slot 14, after its primitives)
 #pragma unroll
-        for (int k = 0; k < 5; ++k) pr[k] = pp[k * st];
-      }
+      for (int k = 0; k < C::NPR; ++k) pr[k] = pp[(PZ && bnd ? 4 + k : prow(k)) * st];
     }
   };
   constexpr int NPRX = C::NPR > 0 ? C::NPR : 1;
-  // primitives (SR: velocity and pressure; MHD: given) and wave quantities
-  auto state_waves = [&](const double *u, double p, Prim &P, WaveState &w) {
+  // primitives (of SR and PZ: velocity and pressure) and wave quantities of a
+  // state from U and the rows it carries
+  auto state_waves = [&](const double *u, const double *pr, Prim &P, WaveState &w) {
     if constexpr (SYS == kSR) {
-      P = sr_wave_state(u, p, A.gamma, w);
+      P = sr_wave_state(u, pr[0], A.gamma, w);
+    } else if constexpr (PZ) {
+      P = mhd_wave_state(u, pr[0], pr[1], A.gamma, w);
     } else {
-      if constexpr (SYS == kNE) P = prims_at_pressure<kNE>(u, A.gamma, 0.0, A.poly);
+      if constexpr (SYS == kNE) {
+        P = prims_at_pressure<kNE>(u, A.gamma, 0.0, A.poly);
+      } else {
+        P.rho = pr[0]; P.v[0] = pr[1]; P.v[1] = pr[2]; P.v[2] = pr[3]; P.p = pr[4];
+      }
       w = wave_state<SYS>(u, P, A.gamma, A.gratio);
     }
   };
@@ -369,15 +388,11 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
       Prim Pi;
 #pragma unroll
       for (int v = 0; v < NV; ++v) ui[v] = own[v * NPE];
-      if (SYS == kMHD) {
-        Pi.rho = own[NV * NPE];
-        Pi.v[0] = own[(NV + 1) * NPE];
-        Pi.v[1] = own[(NV + 2) * NPE];
-        Pi.v[2] = own[(NV + 3) * NPE];
-        Pi.p = own[(NV + 4) * NPE];
-      }
+      double pri[NPRX];
+#pragma unroll
+      for (int k = 0; k < C::NPR; ++k) pri[k] = own[(NV + k) * NPE];
       WaveState wi;
-      state_waves(ui, SYS == kSR ? own[NV * NPE] : 0.0, Pi, wi);
+      state_waves(ui, pri, Pi, wi);
       flux_normal<SYS>(d, ui, Pi, Fi);
 #pragma unroll
       for (int v = 0; v < NV; ++v) slot[v * 6 * NF] = Fi[v];
@@ -398,10 +413,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
       } else {
         load_raw(kind, src, ue, pr);
       }
-      if (SYS == kMHD) {
-        Pe.rho = pr[0]; Pe.v[0] = pr[1]; Pe.v[1] = pr[2]; Pe.v[2] = pr[3]; Pe.p = pr[4];
-      }
-      state_waves(ue, SYS == kSR ? pr[0] : 0.0, Pe, we);
+      state_waves(ue, pr, Pe, we);
     }
     flux_normal<SYS>(d, ue, Pe, Fe);
     if constexpr ((FLUX == kMarquina || FLUX == kRoe) && SYS == kNE) {
@@ -485,7 +497,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
 #pragma unroll
     for (int v = 0; v < NV; ++v) ur[v] = own_row(A.U, v)[oq];
 #pragma unroll
-    for (int k = 0; k < C::NPR; ++k) prr[k] = own_row(A.P, SYS == kSR ? 4 : k)[oq];
+    for (int k = 0; k < C::NPR; ++k) prr[k] = own_row(A.P, prow(k))[oq];
 #pragma unroll
     for (int v = 0; v < NV; ++v) mybuf[v * NPE + a] = ur[v];
 #pragma unroll
@@ -522,16 +534,12 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
   if (active) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) u[v] = mybuf[v * NPE + a];
-    if (SYS == kMHD) {
-      P.rho = mybuf[NV * NPE + a];
-      P.v[0] = mybuf[(NV + 1) * NPE + a];
-      P.v[1] = mybuf[(NV + 2) * NPE + a];
-      P.v[2] = mybuf[(NV + 3) * NPE + a];
-      P.p = mybuf[(NV + 4) * NPE + a];
-      acc[8] = -A.kappa * u[8];
-    } else {
-      P = prims_at_pressure<SYS>(u, A.gamma, SYS == kSR ? mybuf[NV * NPE + a] : 0.0, A.poly);
-    }
+    double prr[NPRX];
+#pragma unroll
+    for (int k = 0; k < C::NPR; ++k) prr[k] = mybuf[(NV + k) * NPE + a];
+    WaveState w;  // (unused here)
+    state_waves(u, prr, P, w);
+    if (SYS == kMHD) acc[8] = -A.kappa * u[8];
   } else {
 #pragma unroll
     for (int v = 0; v < NV; ++v) u[v] = 0.0;
@@ -658,18 +666,24 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
   }
   combine();
   const C2PResult R = recover<SYS>(us, A.gamma, P.p, 0.0, 100, A.poly);
-  // intermediate stages of NE / SR keep only the pressure (the next stage
-  // rebuilds the rest); SRMHD and the caller's buffers get all five rows
-  if (SYS == kMHD) {
-    A.Pout[q] = R.P.rho;
-    A.Pout[nn + q] = R.P.v[0];
-    A.Pout[2 * nn + q] = R.P.v[1];
-    A.Pout[3 * nn + q] = R.P.v[2];
-  } else if (A.full_prims) {  // rows the next stage does not read: streamed
-    __builtin_nontemporal_store(R.P.rho, &A.Pout[q]);
-    __builtin_nontemporal_store(R.P.v[0], &A.Pout[nn + q]);
-    __builtin_nontemporal_store(R.P.v[1], &A.Pout[2 * nn + q]);
-    __builtin_nontemporal_store(R.P.v[2], &A.Pout[3 * nn + q]);
+  // intermediate stages keep only what the next one reads: the pressure and,
+  // on uniform SRMHD meshes, z in row 0 (mixed ones keep all five rows); the
+  // caller's buffers get all five
+  if (A.full_prims || (SYS == kMHD && MIXED)) {  // rows the next stage does not read: streamed
+    if (SYS == kMHD && MIXED && !A.full_prims) {
+      A.Pout[q] = R.P.rho;
+      A.Pout[nn + q] = R.P.v[0];
+      A.Pout[2 * nn + q] = R.P.v[1];
+      A.Pout[3 * nn + q] = R.P.v[2];
+      asm volatile("");
+    } else {
+      __builtin_nontemporal_store(R.P.rho, &A.Pout[q]);
+      __builtin_nontemporal_store(R.P.v[0], &A.Pout[nn + q]);
+      __builtin_nontemporal_store(R.P.v[1], &A.Pout[2 * nn + q]);
+      __builtin_nontemporal_store(R.P.v[2], &A.Pout[3 * nn + q]);
+    }
+  } else if (SYS == kMHD) {
+    A.Pout[q] = R.z;
   }
   A.Pout[4 * nn + q] = R.P.p;
   if (!R.ok) atomicAdd(A.nfail, 1ull);
@@ -679,7 +693,9 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
 // per workgroup, one thread per volume node.
 // The RK stages of 64^3 SRMHD elements of degree 3 (16.8M nodes): 1.73 -> 1.50
 // ms a stage on average since the first stage does not read U^n (weight 0; its
-// lines had left L2 by then) and large meshes stream U^n and the output.
+// lines had left L2 by then) and large meshes stream U^n and the output, ->
+// 1.32 ms with two rows between the stages instead of five (p and z; 28 rows
+// a stage on average instead of 34) and two elements per workgroup.
 // The operator on 32^3 elements of degree 4 (SR): 552 vector instructions per
 // wave and 68 VGPRs (7 waves per SIMD), 111 us at 4.1 TB/s of counted traffic,
 // of the 4.6 TB/s a large copy reaches here; with the neighbours found per
@@ -688,10 +704,10 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
 // (SR hydro is held to six waves per SIMD: its limited stage would take more
 // than 80 VGPRs, which was slower.)
 template <int SYS, int N, int STAGE, int EPB_ = default_epb<SYS, N>(), bool MIXED = false, int FLUX = kLLF,
-          bool MOM = false>
+          bool MOM = false, bool PZ = false>
 __global__ void __launch_bounds__((RhsCfg<SYS, N, EPB_>::THREADS)) __attribute__((amdgpu_waves_per_eu(SYS == kSR ? 6 : 1)))
 rhs_kernel(const RhsArgs A) {
-  using C = RhsCfg<SYS, N, EPB_, FLUX>;
+  using C = RhsCfg<SYS, N, EPB_, FLUX, PZ>;
   __shared__ double smem[C::LDS + (MOM ? C::EPB * C::NPE : 0)];
   // XCD-major block order: hardware block b runs on XCD b % 8, which walks
   // its own contiguous range of the processing order.
@@ -700,7 +716,7 @@ rhs_kernel(const RhsArgs A) {
   if (seq >= A.nblocks) return;
   int grp = seq;
   if constexpr (!MIXED) grp = A.bm.S ? brick_map(seq, A.bm) : seq;
-  rhs_body<SYS, N, STAGE, EPB_, MIXED, C::THREADS, FLUX, MOM>(A, grp, smem);
+  rhs_body<SYS, N, STAGE, EPB_, MIXED, C::THREADS, FLUX, MOM, PZ>(A, grp, smem);
 }
 
 // The RK stage that also writes the limiter's moments.
@@ -729,6 +745,9 @@ hipError_t launch_one(int stage, const RhsArgs &a, hipStream_t s) {
   const int grid = ((b.nblocks + 7) / 8) * 8;
   if (stage == 0)
     hipLaunchKernelGGL((rhs_kernel<SYS, N, 0, C::EPB, false, FLUX>), dim3(grid), dim3(C::THREADS), 0, s, b);
+  else if (SYS == kMHD && a.in_pz)
+    hipLaunchKernelGGL((rhs_kernel<SYS, N, 1, C::EPB, false, FLUX, false, SYS == kMHD>), dim3(grid), dim3(C::THREADS), 0,
+                       s, b);
   else
     hipLaunchKernelGGL((rhs_kernel<SYS, N, 1, C::EPB, false, FLUX>), dim3(grid), dim3(C::THREADS), 0, s, b);
   return hipGetLastError();

@@ -79,3 +79,33 @@ def test_operator_fixed_faces_one_direction(ora, dg, system, N, direction):
     dU = G.empty_state()
     dg.dg_rhs(G, to_dev(U), to_dev(prim * (1 + 1e-3)), dU)
     assert np.all(normwise_err(to_host(dU), dUo, floor_scale=np.abs(dUo).max()) <= 1e-12)
+
+
+# SRMHD stages pass pressure and z = rho h W^2 to the next stage; odd element
+# counts leave the second element of the last workgroup empty
+@pytest.mark.parametrize("nel", [(3, 1, 1), (3, 3, 1)])
+@pytest.mark.parametrize("N", [1, 3, 4, 5])
+@pytest.mark.parametrize("faces", ["periodic", "fixed"])
+def test_srmhd_step(ora, dg, N, nel, faces):
+    """One RK3 step against the oracle: 2e-12 dt max|L| + 8 ulp max|U| per
+    variable (the operator bound through three stages, plus the rounding of
+    the Shu-Osher combinations), scales taken over all variables."""
+    g = GAMMA[MHD]
+    lo, hi = [1.0, 0.1, -0.2, 0.05, 1.0, 0.5, 0.2, -0.1, 0.03], [0.7, -0.1, 0.3, 0.2, 2.0, 0.4, -0.2, 0.3, -0.05]
+    bc = {0: (tuple(lo), tuple(hi))} if faces == "fixed" else None
+    m = ora.mesh(MHD, nel, N, g, lo=LO, hi=HI, kappa=0.5, bc=bc)
+    G = dg.Mesh(MHD, nel, N, g, lo=LO, hi=HI, kappa=0.5)
+    if bc:
+        dg.dgmi_set_boundary(G, 0, lo, hi)
+    U, prim = _state(ora, MHD, m, seed=3 + N)
+    L, _, nf = ora.rhs(m, U)
+    assert nf == 0
+    dt = 1e-3 * np.abs(U).max() / np.abs(L).max()
+    Uo, nf = ora.step(m, U, dt)
+    assert nf == 0
+    Ud, Pd = to_dev(U), to_dev(prim)
+    dg.dg_step(G, Ud, Pd, dt)
+    assert dg.dgmi_failures(G) == 0
+    assert np.abs(to_host(Ud) - Uo).max() <= 2e-12 * dt * np.abs(L).max() + 8 * 2.0 ** -52 * np.abs(U).max()
+    _, Po, _ = ora.rhs(m, to_host(Ud))
+    assert np.all(normwise_err(to_host(Pd), Po) <= 1e-12)
