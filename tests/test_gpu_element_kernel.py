@@ -100,7 +100,7 @@ def test_srmhd_step(ora, dg, N, nel, faces):
     U, prim = _state(ora, MHD, m, seed=3 + N)
     L, _, nf = ora.rhs(m, U)
     assert nf == 0
-    dt = 1e-3 * np.abs(U).max() / np.abs(L).max()
+    dt = 1e-5 * np.abs(U).max() / np.abs(L).max()
     Uo, nf = ora.step(m, U, dt)
     assert nf == 0
     Ud, Pd = to_dev(U), to_dev(prim)
