@@ -537,7 +537,7 @@ static dgmi_status mixed_pass(dgmi_ctx *c, int stage, const double *U, const dou
   return element_pass(c, stage, a, c->single_launch, s, mom);
 }
 
-static dgmi::LimArgs lim_args(dgmi_ctx *c, double *U, const double *Pseed, double *Pout);
+static dgmi::LimArgs lim_args(dgmi_ctx *c, double *U, const double *Pseed, double *Pout, int full_prims);
 
 // The intermediate states of an SSP-RK3 step: U^(1), U^(2) [nv][nnodes] and
 // their primitives [5][nnodes].
@@ -550,12 +550,12 @@ static RkBufs ctx_bufs(dgmi_ctx *c) { return RkBufs{c->d_U1, c->d_U2, c->d_P1, c
 // per degree); P seeds the recoveries and receives the primitives.
 // moments = false: a limited stage kernel already wrote the moments, the
 // unphysical-node flags and every node's primitives.
-static dgmi_status mixed_limit(dgmi_ctx *c, double *U, double *P, hipStream_t s, bool moments = true) {
+static dgmi_status mixed_limit(dgmi_ctx *c, double *U, double *P, hipStream_t s, bool moments = true,
+                               int full_prims = 1) {
   if (!c->lim_tab_ready || !c->d_limtab_mix || !c->d_mom || !c->d_bad)
     return fail(DGMI_EINVAL, "limiter: tables or scratch missing (dgmi_set_limiter did not complete)");
-  dgmi::LimArgs a = lim_args(c, U, P, P);
+  dgmi::LimArgs a = lim_args(c, U, P, P, full_prims);
   a.off = c->d_off;
-  a.deg = c->d_deg;
   HIP_TRY(dgmi::launch_limiter_mixed(c->sys, moments, c->lstart, c->lcount, c->d_elist, c->d_limtab_mix, a, s));
   return DGMI_OK;
 }
@@ -568,9 +568,9 @@ static dgmi_status mixed_step_enqueue(dgmi_ctx *c, double *U, double *P, const R
   if (limit && (!c->lim_tab_ready || !c->d_limtab_mix || !c->d_mom || !c->d_bad))
     return fail(DGMI_EINVAL, "limiter: tables or scratch missing (dgmi_set_limiter did not complete)");
   dgmi_status st = mixed_pass(c, 1, U, P, b.U1, U, b.P1, 0.0, 1.0, 0, s, limit);
-  if (st == DGMI_OK && limit) st = mixed_limit(c, b.U1, b.P1, s, false);
+  if (st == DGMI_OK && limit) st = mixed_limit(c, b.U1, b.P1, s, false, 0);
   if (st == DGMI_OK) st = mixed_pass(c, 1, b.U1, b.P1, b.U2, U, b.P2, 0.75, 0.25, 0, s, limit);
-  if (st == DGMI_OK && limit) st = mixed_limit(c, b.U2, b.P2, s, false);
+  if (st == DGMI_OK && limit) st = mixed_limit(c, b.U2, b.P2, s, false, 0);
   if (st == DGMI_OK) st = mixed_pass(c, 1, b.U2, b.P2, U, U, P, 1.0 / 3.0, 2.0 / 3.0, 1, s, limit);
   if (st == DGMI_OK && limit) st = mixed_limit(c, U, P, s, false);
   return st;
@@ -912,8 +912,9 @@ static dgmi_status boundary_pass(dgmi_ctx *c, double t, hipStream_t s) {
   return DGMI_OK;
 }
 
-static dgmi::LimArgs lim_args(dgmi_ctx *c, double *U, const double *Pseed, double *Pout) {
+static dgmi::LimArgs lim_args(dgmi_ctx *c, double *U, const double *Pseed, double *Pout, int full_prims) {
   dgmi::LimArgs a{};
+  a.full_prims = full_prims;
   a.U = U;
   a.Pseed = Pseed;
   a.Pout = Pout;
@@ -1051,7 +1052,7 @@ static dgmi_status step_impl(dgmi_ctx *ctx, double *U, double *prim_inout, doubl
     a.lim_h = ctx->d_limtab;
     a.lim_mu = ctx->d_limtab + 8;
     HIP_TRY(dgmi::launch_rhs_stage_moments(ctx->sys, ctx->degree, flux_of(ctx), a, s));
-    HIP_TRY(dgmi::launch_limiter(ctx->sys, ctx->degree, false, lim_args(ctx, out, Pout, Pout), s));
+    HIP_TRY(dgmi::launch_limiter(ctx->sys, ctx->degree, false, lim_args(ctx, out, Pout, Pout, a.full_prims), s));
     return DGMI_OK;
   };
   dgmi_status st;
@@ -1293,7 +1294,7 @@ dgmi_status dg_limit(dgmi_ctx *ctx, double *U, double *prim_inout, void *stream)
   if (!is_device_ptr(U) || !is_device_ptr(prim_inout) || U == prim_inout)
     return fail(DGMI_EINVAL, "dg_limit: U and prim_inout must be distinct device pointers");
   if (ctx->mixed) return mixed_limit(ctx, U, prim_inout, (hipStream_t)stream);
-  HIP_TRY(dgmi::launch_limiter(ctx->sys, ctx->degree, true, lim_args(ctx, U, prim_inout, prim_inout),
+  HIP_TRY(dgmi::launch_limiter(ctx->sys, ctx->degree, true, lim_args(ctx, U, prim_inout, prim_inout, 1),
                                (hipStream_t)stream));
   return DGMI_OK;
 }
@@ -1402,7 +1403,7 @@ dgmi_status dg_step_ab3(dgmi_ctx *ctx, double *U, double *prim_inout, double dt,
         st = mixed_limit(ctx, U, prim_inout, s);
         if (st != DGMI_OK) return st;
       } else {
-        HIP_TRY(dgmi::launch_limiter(ctx->sys, ctx->degree, true, lim_args(ctx, U, prim_inout, prim_inout), s));
+        HIP_TRY(dgmi::launch_limiter(ctx->sys, ctx->degree, true, lim_args(ctx, U, prim_inout, prim_inout, 1), s));
       }
     }
     ctx->time += dt;

@@ -125,16 +125,16 @@ struct LimArgs {
   // fixing of every node of an element with a limited component)
   double fix_D, fix_tau;
   unsigned long long *nfix;   // nodes changed by the fixing
-  // mixed-degree meshes: the elements of one degree (elist, nlist), every
-  // element's first node (off) and degree (deg; null on uniform meshes)
+  int full_prims;             // write all five primitive rows (NE / SR between RK stages: only the pressure)
+  // mixed-degree meshes: the elements of one degree (elist, nlist) and every
+  // element's first node (off)
   const int32_t *elist;
   int64_t nlist;
   const int64_t *off;
-  const int32_t *deg;
 };
 // The limiter on a mixed-degree mesh: moments per degree over the elements of
-// that degree (elist_all + lstart[N], lcount[N] of them), the decisions over
-// every element, the rewrite per degree.  tabs: per degree N the 24 doubles
+// that degree (elist_all + lstart[N], lcount[N] of them), then decisions and
+// rewrite per degree.  tabs: per degree N the 24 doubles
 // w/2, 3/2 int(ell xi), GLL node at tabs + 24 N.
 // moments = false: the limited mixed stage kernel already wrote the moments,
 // flags and primitives.

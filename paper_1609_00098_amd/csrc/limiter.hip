@@ -1,7 +1,7 @@
 // Minmod-family slope limiter (high-resolution shock-capturing section:
 // eqs. MinModSol, MinModB, MinMod and the generalized troubled-cell test),
-// on uniform meshes, in three steps with grid-wide dependencies between
-// them (a limited element needs its neighbours' means):
+// on uniform meshes, in two steps with a grid-wide dependency between them
+// (a limited element needs its neighbours' means):
 //
 //   moments   one thread per node: recover the node's primitives (seeded
 //       with the pressure of the state the stage started from), flag the
@@ -11,15 +11,22 @@
 //       face means.  Inside dg_step the RK stage kernel does this itself on
 //       the state it has just formed (limiter_moments_kernel serves
 //       dg_limit).
-//   decide    one thread per (element, component): from the moments of the
-//       element and its six neighbours (or a box face's fixed exterior
-//       state), whether the component is troubled and its limited slopes,
-//       written over the element's moments.
-//   apply     one thread per node of an element with a troubled component:
+//   apply     first one thread per (element, component): from the moments of
+//       the element and its six neighbours (or a box face's fixed exterior
+//       state), whether the component is troubled and its limited slopes;
+//       then one thread per node of an element with a troubled component:
 //       rewrite the troubled components as U0 + sum_d a_d (x_d - x_d0), pass
 //       the node through the conserved-variable fixing when it is switched
 //       on (relativistic systems), and recover the node's primitives.  Other
-//       elements read one flag per component and touch no node data.
+//       elements touch no node data.
+//
+// Between RK stages only the pressure row of the primitives is read (NE, SR),
+// so only that row is written there (full_prims of LimArgs).  A limited step
+// of 32^3 SR elements of degree 4, half of the components troubled, took
+// 1,039 us with all five rows written everywhere, a launch of its own for the
+// decisions and moments summed a face per thread, 870 us now (stage 250 -> 190
+// us, decisions and rewrite 106 -> 100 us, bound by the recovery's vector
+// instructions and the chain of neighbour loads in front of it).
 //
 // Per component k of element e and direction d (every direction has degree
 // N >= 1 on a uniform mesh):
@@ -50,11 +57,13 @@ struct LimCfg {
   static constexpr int THREADS = ((EPB * NPE + 63) / 64) * 64;
 };
 
-__device__ __forceinline__ void store_prims(double *Pout, int64_t nn, int64_t q, const Prim &P) {
-  Pout[q] = P.rho;
-  Pout[nn + q] = P.v[0];
-  Pout[2 * nn + q] = P.v[1];
-  Pout[3 * nn + q] = P.v[2];
+__device__ __forceinline__ void store_prims(double *Pout, int64_t nn, int64_t q, const Prim &P, bool all) {
+  if (all) {
+    Pout[q] = P.rho;
+    Pout[nn + q] = P.v[0];
+    Pout[2 * nn + q] = P.v[1];
+    Pout[3 * nn + q] = P.v[2];
+  }
   Pout[4 * nn + q] = P.p;
 }
 
@@ -65,7 +74,7 @@ __global__ void __launch_bounds__((LimCfg<SYS, N>::THREADS)) limiter_moments_ker
   using C = LimCfg<SYS, N>;
   constexpr int NP = C::NP, NPE = C::NPE, NF = C::NF, NV = C::NV, EPB = C::EPB;
   __shared__ double su[EPB * NV * NPE];
-  __shared__ double lines[4 * EPB * NV * NF];
+  __shared__ double lines[EPB * NV * (4 * NF + NP)];
   __shared__ double sh[NP], smu[NP];
   __shared__ int sbad[EPB];
   const int tid = threadIdx.x;
@@ -89,7 +98,7 @@ __global__ void __launch_bounds__((LimCfg<SYS, N>::THREADS)) limiter_moments_ker
       su[(le * NV + v) * NPE + a] = u[v];
     }
     const C2PResult R = recover<SYS>(u, A.gamma, A.Pseed[4 * nn + q], 0.0, 100, A.poly);
-    store_prims(A.Pout, nn, q, R.P);
+    store_prims(A.Pout, nn, q, R.P, true);
     if (!R.ok) sbad[le] = 1;
   }
   __syncthreads();
@@ -97,48 +106,37 @@ __global__ void __launch_bounds__((LimCfg<SYS, N>::THREADS)) limiter_moments_ker
   if (tid < EPB && e0 + tid < cnt) A.bad[MIXED ? (int64_t)A.elist[e0 + tid] : e0 + tid] = sbad[tid];
 }
 
-// One thread per (element, component): troubled or not, and the limited
-// slopes, written over the element's moments (slots 1..3: a_x, a_y, a_z;
-// slot 4: 1 when troubled).  Reads only the element's own slots and the
-// neighbours' means (slot 0), which nothing here overwrites.
+// Whether component v of element e (degree N) is troubled, and its limited
+// slopes ad[3].  Reads the element's own moments and its neighbours' means.
 template <int N, int NV>
-__global__ void __launch_bounds__(256) limiter_decide_kernel(const LimArgs A) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  int troubled = 0;
-  if (t < A.nelem * NV) {
-    const int64_t e = t / NV;
-    const int v = (int)(t - e * NV);
-    double *me = A.mom + e * 10 * NV;
-    const double u0 = me[v];
-    troubled = A.bad[e] != 0;
-    // the troubled-cell test from degree 2 on (per element on mixed meshes)
-    const bool high = A.deg ? A.deg[e] >= 2 : N >= 2;
-    double ad[3];
+__device__ __forceinline__ bool limiter_decide(const LimArgs &A, int64_t e, int v, double *ad) {
+  const double *me = A.mom + e * 10 * NV;
+  int32_t nb[6];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const int32_t elo = A.nbr[e * 6 + 2 * d], ehi = A.nbr[e * 6 + 2 * d + 1];
-      const double nlo = elo >= 0 ? A.mom[(int64_t)elo * 10 * NV + v] : A.bcs[(2 * d) * 16 + v];
-      const double nhi = ehi >= 0 ? A.mom[(int64_t)ehi * 10 * NV + v] : A.bcs[(2 * d + 1) * 16 + v];
-      const double dx = A.dx[d];
-      const double a1 = me[(1 + d) * NV + v] * (2.0 / dx);
-      ad[d] = minmodB(a1, (nhi - u0) * A.beta / dx, (u0 - nlo) * A.beta / dx, A.M, dx);
-      if (high) {
-        const double fl = me[(4 + 2 * d) * NV + v], fr = me[(5 + 2 * d) * NV + v];
-        const double vl = u0 - minmod3(u0 - fl, u0 - nlo, nhi - u0);
-        const double vr = u0 + minmod3(fr - u0, u0 - nlo, nhi - u0);
-        if (fabs(vl - fl) > 1e-8 || fabs(vr - fr) > 1e-8) troubled = 1;
-      } else if (ad[d] != a1) {
-        troubled = 1;
-      }
+  for (int f = 0; f < 6; ++f) nb[f] = A.nbr[e * 6 + f];
+  double m[10], mean[6];
+#pragma unroll
+  for (int k = 0; k < 10; ++k) m[k] = me[k * NV + v];
+#pragma unroll
+  for (int f = 0; f < 6; ++f) mean[f] = nb[f] >= 0 ? A.mom[(int64_t)nb[f] * 10 * NV + v] : A.bcs[f * 16 + v];
+  bool troubled = A.bad[e] != 0;
+  const double u0 = m[0];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const double nlo = mean[2 * d], nhi = mean[2 * d + 1];
+    const double dx = A.dx[d];
+    const double a1 = m[1 + d] * (2.0 / dx);
+    ad[d] = minmodB(a1, (nhi - u0) * A.beta / dx, (u0 - nlo) * A.beta / dx, A.M, dx);
+    if (N >= 2) {  // the troubled-cell test
+      const double fl = m[4 + 2 * d], fr = m[5 + 2 * d];
+      const double vl = u0 - minmod3(u0 - fl, u0 - nlo, nhi - u0);
+      const double vr = u0 + minmod3(fr - u0, u0 - nlo, nhi - u0);
+      if (fabs(vl - fl) > 1e-8 || fabs(vr - fr) > 1e-8) troubled = true;
+    } else if (ad[d] != a1) {
+      troubled = true;
     }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) me[(1 + d) * NV + v] = ad[d];
-    me[4 * NV + v] = troubled ? 1.0 : 0.0;
   }
-  // one counter update per wave, spread over 64 counters (A.nlim[64], summed
-  // by the host) so that the atomics do not serialise on one address
-  const unsigned long long bal = __ballot(troubled);
-  if ((threadIdx.x & 63) == 0 && bal) atomicAdd(A.nlim + (blockIdx.x & 63), (unsigned long long)__popcll(bal));
+  return troubled;
 }
 
 template <int SYS, int N, bool MIXED = false>
@@ -146,9 +144,10 @@ __global__ void __launch_bounds__((LimCfg<SYS, N>::THREADS)) limiter_apply_kerne
   using C = LimCfg<SYS, N>;
   constexpr int NP = C::NP, NPE = C::NPE, NV = C::NV, EPB = C::EPB;
   __shared__ double sa[EPB * NV * 4];
-  __shared__ int strb[EPB * NV], sany[EPB];
+  __shared__ int strb[EPB * NV], sany[EPB], scount;
   const int tid = threadIdx.x;
   if (tid < EPB) sany[tid] = 0;
+  if (tid == 0) scount = 0;
   __syncthreads();
   const int64_t e0 = (int64_t)blockIdx.x * EPB;
   const int64_t cnt = MIXED ? A.nlist : A.nelem;
@@ -157,18 +156,22 @@ __global__ void __launch_bounds__((LimCfg<SYS, N>::THREADS)) limiter_apply_kerne
     const int64_t sl = e0 + le;
     if (sl >= cnt) continue;
     const int64_t e = MIXED ? (int64_t)A.elist[sl] : sl;
-    const double *me = A.mom + e * 10 * NV;
-    const bool tr = me[4 * NV + v] != 0.0;
+    double ad[3];
+    const bool tr = limiter_decide<N, NV>(A, e, v, ad);
     strb[t] = tr;
     if (tr) {
-      sa[t * 4] = me[v];
-      sa[t * 4 + 1] = me[NV + v];
-      sa[t * 4 + 2] = me[2 * NV + v];
-      sa[t * 4 + 3] = me[3 * NV + v];
+      sa[t * 4] = A.mom[e * 10 * NV + v];
+      sa[t * 4 + 1] = ad[0];
+      sa[t * 4 + 2] = ad[1];
+      sa[t * 4 + 3] = ad[2];
       sany[le] = 1;
+      atomicAdd(&scount, 1);
     }
   }
   __syncthreads();
+  // one counter update per workgroup, spread over 64 counters (A.nlim[64],
+  // summed by the host) so that the atomics do not serialise on one address
+  if (tid == 0 && scount) atomicAdd(A.nlim + (blockIdx.x & 63), (unsigned long long)scount);
   const int le = tid / NPE, a = tid - le * NPE;
   const int64_t sl = e0 + le;
   if (le >= EPB || sl >= cnt || !sany[le]) return;
@@ -196,7 +199,7 @@ __global__ void __launch_bounds__((LimCfg<SYS, N>::THREADS)) limiter_apply_kerne
     }
   }
   const C2PResult R = recover<SYS>(u, A.gamma, A.Pout[4 * nn + q], 0.0, 100, A.poly);
-  store_prims(A.Pout, nn, q, R.P);
+  store_prims(A.Pout, nn, q, R.P, SYS == kMHD || A.full_prims);
   if (!R.ok) atomicAdd(A.nfail, 1ull);
 }
 
@@ -241,17 +244,13 @@ template <int SYS, int N>
 static hipError_t launch_lim_n(bool moments, const LimArgs &a, hipStream_t s) {
   using C = LimCfg<SYS, N>;
   const int64_t nb = (a.nelem + C::EPB - 1) / C::EPB;
-  const int64_t nd = (a.nelem * C::NV + 255) / 256;
-  if (nb > ((int64_t)1 << 30) || nd > ((int64_t)1 << 30)) return hipErrorInvalidValue;
+  if (nb > ((int64_t)1 << 30)) return hipErrorInvalidValue;
   if (nb == 0) return hipSuccess;
   if (moments) {
     hipLaunchKernelGGL((limiter_moments_kernel<SYS, N>), dim3((unsigned)nb), dim3(C::THREADS), 0, s, a);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
   }
-  hipLaunchKernelGGL((limiter_decide_kernel<(N >= 2 ? 2 : 1), C::NV>), dim3((unsigned)nd), dim3(256), 0, s, a);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
   hipLaunchKernelGGL((limiter_apply_kernel<SYS, N>), dim3((unsigned)nb), dim3(C::THREADS), 0, s, a);
   return hipGetLastError();
 }
@@ -292,18 +291,9 @@ static hipError_t lim_mixed_n(bool apply, LimArgs a, const int64_t *lstart, cons
 template <int SYS>
 static hipError_t lim_mixed_sys(bool moments, const int64_t *lstart, const int64_t *lcount, const int32_t *elist_all,
                                 const double *tabs, const LimArgs &a, hipStream_t s) {
-  if (!a.deg || !a.off) return hipErrorInvalidValue;
+  if (!a.off) return hipErrorInvalidValue;
   for (int pass = moments ? 0 : 1; pass < 2; ++pass) {
     const bool apply = pass == 1;
-    if (apply) {  // decisions over every element, each with its own degree
-      const int64_t nd = (a.nelem * SysTraits<SYS>::nv + 255) / 256;
-      if (nd > ((int64_t)1 << 30)) return hipErrorInvalidValue;
-      if (nd > 0) {
-        hipLaunchKernelGGL((limiter_decide_kernel<2, SysTraits<SYS>::nv>), dim3((unsigned)nd), dim3(256), 0, s, a);
-        const hipError_t err = hipGetLastError();
-        if (err != hipSuccess) return err;
-      }
-    }
     hipError_t err;
     if ((err = lim_mixed_n<SYS, 1>(apply, a, lstart, lcount, elist_all, tabs, s)) != hipSuccess) return err;
     if ((err = lim_mixed_n<SYS, 2>(apply, a, lstart, lcount, elist_all, tabs, s)) != hipSuccess) return err;

@@ -24,21 +24,22 @@ __device__ __forceinline__ double minmodB(double a1, double a2, double a3, doubl
 // whose nodal values sit in LDS as su[EPB][NV][(N+1)^3]: the mean, the
 // Legendre slope coefficients c_x, c_y, c_z (3/2 of the first moment along
 // the direction, weighted means across it) and the face means -x, +x, -y,
-// +y, -z, +z, written to mom[e][10][NV].  Two levels: every x-line is first
+// +y, -z, +z, written to mom[e][10][NV].  Three levels of sums over at most
+// N + 1 terms each, so that no thread walks a whole face: every x-line is
 // reduced to its weighted sum A, its first moment B (mirror nodes paired:
 // the first-moment weights are odd about the element centre, so a line on
-// which U is constant gives exactly zero) and its two end values; then each
-// moment is a sum over at most (N+1)^2 line results.  sh = w/2 and
-// smu = 3/2 int(ell xi) per node index (LDS); lines: LDS scratch of
-// 4 EPB NV (N+1)^2 doubles.  The block holds slots e0 .. e0+EPB-1 of nelem;
-// slot k is element eids[k] (mixed-degree lists) or k itself (eids null).
-// Every thread of the block must call it.
+// which U is constant gives exactly zero) and its two end values; those over
+// y to plane sums; those over z.  sh = w/2 and smu = 3/2 int(ell xi) per node
+// index (LDS); lines: LDS scratch of EPB NV (4 (N+1)^2 + N+1) doubles; su is
+// overwritten.  The block holds slots e0 .. e0+EPB-1 of nelem; slot k is
+// element eids[k] (mixed-degree lists) or k itself (eids null).  Every thread
+// of the block must call it.
 template <int N, int NV, int EPB, int BT>
-__device__ __forceinline__ void element_moments(const double *su, double *lines, const double *sh,
-                                                const double *smu, double *mom, int64_t e0, int64_t nelem,
-                                                const int32_t *eids = nullptr) {
+__device__ __forceinline__ void element_moments(double *su, double *lines, const double *sh, const double *smu,
+                                                double *mom, int64_t e0, int64_t nelem, const int32_t *eids = nullptr) {
   constexpr int NP = N + 1, NF = NP * NP, NPE = NP * NF;
   const int tid = threadIdx.x;
+  double *const slopes = lines + EPB * NV * 4 * NF;  // [EPB NV][NP] y-pair sums of A per plane
   for (int t = tid; t < EPB * NV * NF; t += BT) {
     const int le = t / (NV * NF), r = t - le * NV * NF, v = r / NF, jk = r - v * NF;
     if (e0 + le >= nelem) continue;
@@ -55,29 +56,42 @@ __device__ __forceinline__ void element_moments(const double *su, double *lines,
     L[3 * NF + jk] = line[N];
   }
   __syncthreads();
+  // planes of constant z: weighted sums over y of A, B and the end values into
+  // su as [element, component][4][NP], and the y-slope sums of A
+  for (int t = tid; t < EPB * NV * 5 * NP; t += BT) {
+    const int c = t / (5 * NP), r = t - c * 5 * NP, x = r / NP, k = r - x * NP;
+    if (e0 + c / NV >= nelem) continue;
+    const double *X = lines + c * 4 * NF + (x < 4 ? x * NF : 0) + NP * k;
+    double s = 0.0;
+    if (x < 4) {
+#pragma unroll
+      for (int j = 0; j < NP; ++j) s += sh[j] * X[j];
+      su[c * NPE + x * NP + k] = s;
+    } else {
+#pragma unroll
+      for (int j = 0; j < N - j; ++j) s += smu[N - j] * (X[N - j] - X[j]);
+      slopes[c * NP + k] = s;
+    }
+  }
+  __syncthreads();
   for (int t = tid; t < EPB * NV * 10; t += BT) {
     const int le = t / (NV * 10), r = t - le * NV * 10, kind = r / NV, v = r - kind * NV;
     if (e0 + le >= nelem) continue;
-    const double *L = lines + (le * NV + v) * 4 * NF;
-    const double *A = L;
+    const int c = le * NV + v;
+    const double *R = su + c * NPE, *A = lines + c * 4 * NF;
     double s = 0.0;
-    if (kind == 0 || kind == 1 || kind == 4 || kind == 5) {
-      const double *X = kind == 0 ? A : (kind == 1 ? L + NF : (kind == 4 ? L + 2 * NF : L + 3 * NF));
-      for (int k = 0; k < NP; ++k)
-        for (int j = 0; j < NP; ++j) s += sh[j] * sh[k] * X[j + NP * k];
-    } else if (kind == 2 || kind == 3) {
-      // c_y: pairs along j of the x-line sums, then weights along k (c_z: swapped)
-      const int sj = kind == 2 ? 1 : NP, sk = kind == 2 ? NP : 1;
-      for (int k = 0; k < NP; ++k) {
-        double ls = 0.0;
-        for (int j = 0; j < N - j; ++j) ls += smu[N - j] * (A[(N - j) * sj + k * sk] - A[j * sj + k * sk]);
-        s += sh[k] * ls;
-      }
+    if (kind == 3) {  // c_z: mirror planes paired
+#pragma unroll
+      for (int k = 0; k < N - k; ++k) s += smu[N - k] * (R[N - k] - R[k]);
+    } else if (kind >= 8) {  // the z faces are planes
+      s = R[kind == 8 ? 0 : N];
     } else {
-      // y faces: x-line sums at j = 0 or N weighted along k; z faces: at k = 0 or N along j
-      const int f = kind - 6, hi = f & 1;
-      const int sj = f < 2 ? 1 : NP, sk = f < 2 ? NP : 1;
-      for (int k = 0; k < NP; ++k) s += sh[k] * A[(hi ? N : 0) * sj + k * sk];
+      // mean, c_x, c_y, x faces: plane sums; y faces: the x-line sums at j = 0, N
+      const double *X = kind == 2 ? slopes + c * NP
+                                  : (kind >= 6 ? A + (kind == 6 ? 0 : N) : R + NP * (kind < 2 ? kind : kind - 2));
+      const int st = kind >= 6 ? NP : 1;
+#pragma unroll
+      for (int k = 0; k < NP; ++k) s += sh[k] * X[k * st];
     }
     const int64_t eid = eids ? (int64_t)eids[e0 + le] : e0 + le;
     mom[(eid * 10 + kind) * NV + v] = s;

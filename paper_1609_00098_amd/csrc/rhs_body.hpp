@@ -133,7 +133,7 @@ struct RhsCfg {
   static constexpr int RS = NV + NPR;  // rows per element in the volume buffer
   // LDS (doubles): the volume buffer [EPB][RS][NPE] (one direction's nodal
   // fluxes, then each node's state for the face phase), face slots
-  // [EPB][NV][6][NF], D.  (The limited stage adds [EPB][NPE] recovery flags.)
+  // [EPB][NV][6][NF], D.  (The limited stage adds [EPB] flags.)
   static constexpr int VOL = EPB * RS * NPE;
   static constexpr int SLOT = EPB * NV * 6 * NF;
   static constexpr int LDS = VOL + SLOT + NP * NP;  // doubles
@@ -174,7 +174,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
   double *svol = smem;
   double *sslot = svol + C::VOL;
   double *sD = sslot + C::SLOT;
-  double *sflag = sD + NP * NP;  // the limited stage's recovery flags
+  int *badf = (int *)(sD + NP * NP);  // the limited stage: elements with an unrecoverable node
 
   const int tid = threadIdx.x;
   // D for the volume term: loaded here, stored to LDS with the node states
@@ -504,6 +504,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
     for (int k = 0; k < C::NPR; ++k) mybuf[(NV + k) * NPE + a] = prr[k];
   }
   if (tid < NP * NP) sD[tid] = dval;
+  if (MOM && tid < EPB) badf[tid] = 0;
   __syncthreads();
   // ---- face phase: the first round takes the exterior state loaded above
   if (has0) {
@@ -635,18 +636,20 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
   if constexpr (MOM) {
     // limited stage: recover every node of U^(s), then reduce each element to
     // the limiter's moments (the slope limiter runs next, over the grid)
-    double *su = svol, *okf = sflag, *tabs = sD;
+    double *su = svol, *tabs = sD;
     if (active) {
       combine();
 #pragma unroll
       for (int v = 0; v < NV; ++v) su[(le * NV + v) * NPE + a] = us[v];
       const C2PResult R = recover<SYS>(us, A.gamma, P.p, 0.0, 100, A.poly);
-      A.Pout[q] = R.P.rho;
-      A.Pout[nn + q] = R.P.v[0];
-      A.Pout[2 * nn + q] = R.P.v[1];
-      A.Pout[3 * nn + q] = R.P.v[2];
+      if (SYS == kMHD || A.full_prims) {
+        A.Pout[q] = R.P.rho;
+        A.Pout[nn + q] = R.P.v[0];
+        A.Pout[2 * nn + q] = R.P.v[1];
+        A.Pout[3 * nn + q] = R.P.v[2];
+      }
       A.Pout[4 * nn + q] = R.P.p;
-      okf[le * NPE + a] = R.ok ? 1.0 : 0.0;
+      if (!R.ok) badf[le] = 1;
     }
     if (tid < NP) {
       tabs[tid] = A.lim_h[tid];
@@ -656,11 +659,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
     // slots e0 .. e0+EPB-1 of the element list (mixed degrees) or the mesh
     const int64_t e0 = (int64_t)grp * EPB;
     const int64_t nl = MIXED ? A.nlist : A.nelem;
-    if (tid < EPB && e0 + tid < nl) {
-      int bad = 0;
-      for (int b = 0; b < NPE; ++b) bad |= okf[tid * NPE + b] == 0.0;
-      A.bad[MIXED ? (int64_t)A.elist[e0 + tid] : e0 + tid] = bad;
-    }
+    if (tid < EPB && e0 + tid < nl) A.bad[MIXED ? (int64_t)A.elist[e0 + tid] : e0 + tid] = badf[tid];
     element_moments<N, NV, EPB, BT>(su, sslot, tabs, tabs + NP, A.mom, e0, nl, MIXED ? A.elist : nullptr);
     return;
   }
@@ -708,7 +707,7 @@ template <int SYS, int N, int STAGE, int EPB_ = default_epb<SYS, N>(), bool MIXE
 __global__ void __launch_bounds__((RhsCfg<SYS, N, EPB_>::THREADS)) __attribute__((amdgpu_waves_per_eu(SYS == kSR ? 6 : 1)))
 rhs_kernel(const RhsArgs A) {
   using C = RhsCfg<SYS, N, EPB_, FLUX, PZ>;
-  __shared__ double smem[C::LDS + (MOM ? C::EPB * C::NPE : 0)];
+  __shared__ double smem[C::LDS + (MOM ? C::EPB : 0)];
   // XCD-major block order: hardware block b runs on XCD b % 8, which walks
   // its own contiguous range of the processing order.
   const int per = (A.nblocks + 7) >> 3;

@@ -16,25 +16,25 @@ namespace dgmi {
 // costs far less than the occupancy gains.
 constexpr int kAllThreads = 512;
 template <int SYS>
-constexpr int all_budget() {  // doubles of LDS: 52 KB, or one degree-7 element with its flags if larger
-  return RhsCfg<SYS, 7, 1>::LDS + 512 > 6656 ? RhsCfg<SYS, 7, 1>::LDS + 512 : 6656;
+constexpr int all_budget() {  // doubles of LDS: 52 KB, or one degree-7 element with its flag if larger
+  return RhsCfg<SYS, 7, 1>::LDS + 1 > 6656 ? RhsCfg<SYS, 7, 1>::LDS + 1 : 6656;
 }
 // elements per workgroup: as many as fit 512 threads and the budget, with
-// room for the limited stage's recovery flags (one double per node)
+// room for the limited stage's flags (a double per element)
 template <int SYS, int N>
 constexpr int all_epb() {
   constexpr int NP = N + 1, NPE = NP * NP * NP;
   int e = kAllThreads / NPE;
   if (e < 1) e = 1;
-  while (e > 1 && (e * (RhsCfg<SYS, N, 1>::LDS - NP * NP + NPE) + NP * NP) > all_budget<SYS>()) --e;
+  while (e > 1 && (e * (RhsCfg<SYS, N, 1>::LDS - NP * NP + 1) + NP * NP) > all_budget<SYS>()) --e;
   return e;
 }
 // every degree's workgroup, flags included, fits the budget (the LDS layout
 // does not depend on the flux)
-static_assert(RhsCfg<kMHD, 7, 1>::LDS + 512 <= all_budget<kMHD>(), "LDS budget");
-static_assert(RhsCfg<kSR, 7, 1>::LDS + 512 <= all_budget<kSR>(), "LDS budget");
+static_assert(RhsCfg<kMHD, 7, 1>::LDS + 1 <= all_budget<kMHD>(), "LDS budget");
+static_assert(RhsCfg<kSR, 7, 1>::LDS + 1 <= all_budget<kSR>(), "LDS budget");
 static_assert(3 * all_budget<kSR>() * 8 <= 160 * 1024, "three SR workgroups per CU");
-static_assert(RhsCfg<kNE, 7, 1>::LDS + 512 <= all_budget<kNE>(), "LDS budget");
+static_assert(RhsCfg<kNE, 7, 1>::LDS + 1 <= all_budget<kNE>(), "LDS budget");
 static_assert(RhsCfg<kSR, 7, 1, kHLL>::LDS == RhsCfg<kSR, 7, 1, kLLF>::LDS, "LDS layout");
 
 // MOM: the limited RK stage (every node of U^(s) recovered, the limiter's
