@@ -203,7 +203,8 @@ struct dgmi_ctx {
   int bc[3] = {0, 0, 0};          // per direction: 0 periodic, 1 fixed states, 2 analytic
   double time = 0.0;              // time of the state (analytic boundaries)
   double vortex[6] = {0};         // isentropic vortex parameters
-  double *d_bface = nullptr;      // analytic exterior states per boundary face node
+  double *d_bface = nullptr;      // exterior states per boundary face node, bface_copies times
+  int bface_copies = 0;           // 3 with an analytic direction (one per RK stage), else 1
   int64_t boff[7] = {0};
   double hbc[6 * 16] = {0};       // per box face: conserved [0, nv), primitives [9, 14), SRMHD z at 14
   double *d_bc = nullptr;         // device copy
@@ -889,8 +890,9 @@ static dgmi::RhsArgs rhs_args(dgmi_ctx *c) {
   return a;
 }
 
-// Analytic exterior states at time t for every box face of an analytic direction.
-static dgmi_status boundary_pass(dgmi_ctx *c, double t, hipStream_t s) {
+// Analytic exterior states for every box face of an analytic direction at n
+// times (up to bface_copies), the k-th into copy k of the buffer.
+static dgmi_status boundary_pass(dgmi_ctx *c, const double *t, int n, hipStream_t s) {
   if (c->bc[0] != 2 && c->bc[1] != 2 && c->bc[2] != 2) return DGMI_OK;
   dgmi::BoundaryArgs b{};
   b.bface = c->d_bface;
@@ -906,7 +908,8 @@ static dgmi_status boundary_pass(dgmi_ctx *c, double t, hipStream_t s) {
   b.nz = c->nz;
   b.xi = c->d_x + 8 * c->degree;
   b.gamma = c->gamma;
-  b.time = t;
+  b.ntimes = n;
+  for (int k = 0; k < n; ++k) b.time[k] = t[k];
   for (int k = 0; k < 6; ++k) b.par[k] = c->vortex[k];
   HIP_TRY(dgmi::launch_boundary_states(b, s));
   return DGMI_OK;
@@ -960,14 +963,18 @@ dgmi_status dg_rhs(dgmi_ctx *ctx, const double *U, double *prim_inout, double *d
   if (dUdt == U || dUdt == prim_inout) return fail(DGMI_EINVAL, "dg_rhs: dUdt must not alias its inputs");
   hipStream_t s = (hipStream_t)stream;
   const int guess = (ctx->flags & DGMI_FLAG_PLAIN_GUESS) ? DGMI_GUESS_PLAIN : DGMI_GUESS_INPUT;
-  dgmi_status st = recover_all(ctx, U, prim_inout, guess, s);
+  // (the Newtonian operator needs no primitives: it writes them itself)
+  const bool ne = ctx->sys == DGMI_NEWTONIAN_EULER;
+  dgmi_status st = ne ? DGMI_OK : recover_all(ctx, U, prim_inout, guess, s);
   if (st != DGMI_OK) return st;
-  if (ctx->mixed) return mixed_pass(ctx, 0, U, prim_inout, dUdt, nullptr, nullptr, 0.0, 0.0, 0, s);
-  if ((st = boundary_pass(ctx, ctx->time, s)) != DGMI_OK) return st;
+  if (ctx->mixed)
+    return mixed_pass(ctx, 0, U, prim_inout, dUdt, nullptr, ne ? prim_inout : nullptr, 0.0, 0.0, 0, s);
+  if ((st = boundary_pass(ctx, &ctx->time, 1, s)) != DGMI_OK) return st;
   dgmi::RhsArgs a = rhs_args(ctx);
   a.U = U;
   a.P = prim_inout;
   a.out = dUdt;
+  a.Pout = ne ? prim_inout : nullptr;
   HIP_TRY(dgmi::launch_rhs(ctx->sys, ctx->degree, 0, flux_of(ctx), a, s));
   return DGMI_OK;
 }
@@ -978,7 +985,7 @@ dgmi_status dg_operator(dgmi_ctx *ctx, const double *U, const double *prim, doub
     return fail(DGMI_EINVAL, "dg_operator: U, prim and dUdt must be device pointers");
   if (dUdt == U || dUdt == prim) return fail(DGMI_EINVAL, "dg_operator: dUdt must not alias its inputs");
   if (ctx->mixed) return mixed_pass(ctx, 0, U, prim, dUdt, nullptr, nullptr, 0.0, 0.0, 0, (hipStream_t)stream);
-  dgmi_status st = boundary_pass(ctx, ctx->time, (hipStream_t)stream);
+  dgmi_status st = boundary_pass(ctx, &ctx->time, 1, (hipStream_t)stream);
   if (st != DGMI_OK) return st;
   dgmi::RhsArgs a = rhs_args(ctx);
   a.U = U;
@@ -1038,11 +1045,10 @@ static dgmi_status step_impl(dgmi_ctx *ctx, double *U, double *prim_inout, doubl
   // and writes the element moments; the limiter's decide and apply kernels
   // follow (the apply kernel re-recovers the nodes it changes)
   const bool limit = ctx->lim_kind != DGMI_LIMITER_NONE;
-  auto stage = [&](double *out, double *Pout, double t) -> dgmi_status {
+  auto stage = [&](int k, double *out, double *Pout) -> dgmi_status {
     a.out = out;
     a.Pout = Pout;
-    dgmi_status bs = boundary_pass(ctx, t, s);
-    if (bs != DGMI_OK) return bs;
+    if (ctx->bface_copies == 3) a.bface = ctx->d_bface + k * ctx->boff[6] * 16;
     if (!limit) {
       HIP_TRY(dgmi::launch_rhs(ctx->sys, ctx->degree, 1, flux_of(ctx), a, s));
       return DGMI_OK;
@@ -1055,20 +1061,21 @@ static dgmi_status step_impl(dgmi_ctx *ctx, double *U, double *prim_inout, doubl
     HIP_TRY(dgmi::launch_limiter(ctx->sys, ctx->degree, false, lim_args(ctx, out, Pout, Pout, a.full_prims), s));
     return DGMI_OK;
   };
-  dgmi_status st;
   // the stages apply the operator at the times of their inputs: t, t + dt, t + dt/2
-  const double t0 = ctx->time;
+  const double t0 = ctx->time, times[3] = {t0, t0 + dt, t0 + 0.5 * dt};
+  dgmi_status st = boundary_pass(ctx, times, 3, s);
+  if (st != DGMI_OK) return st;
   // stage 1: U1 = U + dt L(U)
   a.U = U; a.P = prim_inout; a.a = 0.0; a.b = 1.0;
-  if ((st = stage(b.U1, b.P1, t0)) != DGMI_OK) return st;
+  if ((st = stage(0, b.U1, b.P1)) != DGMI_OK) return st;
   a.in_pz = ctx->sys == 2 && !limit;
   // stage 2: U2 = 3/4 U + 1/4 (U1 + dt L(U1))
   a.U = b.U1; a.P = b.P1; a.a = 0.75; a.b = 0.25;
-  if ((st = stage(b.U2, b.P2, t0 + dt)) != DGMI_OK) return st;
+  if ((st = stage(1, b.U2, b.P2)) != DGMI_OK) return st;
   // stage 3: U <- 1/3 U + 2/3 (U2 + dt L(U2))  (each thread reads U^n at its own node before writing it)
   a.U = b.U2; a.P = b.P2; a.a = 1.0 / 3.0; a.b = 2.0 / 3.0;
   a.full_prims = 1;
-  if ((st = stage(U, prim_inout, t0 + 0.5 * dt)) != DGMI_OK) return st;
+  if ((st = stage(2, U, prim_inout)) != DGMI_OK) return st;
   ctx->time = t0 + dt;
   return DGMI_OK;
 }
@@ -1102,9 +1109,10 @@ dgmi_status dg_step_noalloc(dgmi_ctx *ctx, double *U, double *prim_inout, double
 }
 
 // Exterior states of every box-face node (16 doubles each), allocated on
-// first use; face f's nodes start at node boff[f].
-static dgmi_status ensure_bface(dgmi_ctx *ctx) {
-  if (ctx->d_bface) return DGMI_OK;
+// first use; face f's nodes start at node boff[f].  copies: 1, or 3 for
+// analytic directions; a buffer that grows keeps its states in every copy.
+static dgmi_status ensure_bface(dgmi_ctx *ctx, int copies) {
+  if (ctx->bface_copies >= copies) return DGMI_OK;
   const int64_t ne[3] = {ctx->nx, ctx->ny, ctx->nz};
   const int64_t nf = (int64_t)(ctx->degree + 1) * (ctx->degree + 1);
   int64_t boff[7];
@@ -1113,13 +1121,22 @@ static dgmi_status ensure_bface(dgmi_ctx *ctx) {
     const int d = f >> 1, da = d == 0 ? 1 : 0, db = d == 2 ? 1 : 2;
     boff[f + 1] = boff[f] + ne[da] * ne[db] * nf;
   }
-  if (hipMalloc(&ctx->d_bface, sizeof(double) * 16 * boff[6]) != hipSuccess ||
-      hipMemset(ctx->d_bface, 0, sizeof(double) * 16 * boff[6]) != hipSuccess) {
+  const size_t one = sizeof(double) * 16 * boff[6];
+  double *buf = nullptr;
+  bool ok = hipMalloc(&buf, one * copies) == hipSuccess;
+  for (int k = 0; ok && k < copies; ++k) {
+    double *to = buf + k * boff[6] * 16;
+    ok = (ctx->d_bface ? hipMemcpy(to, ctx->d_bface, one, hipMemcpyDeviceToDevice) : hipMemset(to, 0, one)) == hipSuccess;
+  }
+  if (!ok) {
     (void)hipGetLastError();
-    (void)hipFree(ctx->d_bface);
-    ctx->d_bface = nullptr;
+    (void)hipFree(buf);
     return fail(DGMI_ENOMEM, "boundary states: device allocation failed");
   }
+  (void)hipDeviceSynchronize();  // no launch reads the old buffer any more
+  (void)hipFree(ctx->d_bface);
+  ctx->d_bface = buf;
+  ctx->bface_copies = copies;
   std::memcpy(ctx->boff, boff, sizeof(boff));
   return DGMI_OK;
 }
@@ -1160,15 +1177,16 @@ dgmi_status dgmi_set_boundary(dgmi_ctx *ctx, int32_t direction, const double *st
   }
   if (bc) {
     // every node of the two box faces gets the face's state
-    dgmi_status st = ensure_bface(ctx);
+    dgmi_status st = ensure_bface(ctx, 1);
     if (st != DGMI_OK) return st;
     for (int side = 0; side < 2; ++side) {
       const int f = 2 * direction + side;
       std::vector<double> rows((size_t)(ctx->boff[f + 1] - ctx->boff[f]) * 16);
       for (size_t r = 0; r < rows.size() / 16; ++r) std::memcpy(&rows[r * 16], hbc + f * 16, 16 * sizeof(double));
-      if (hipMemcpy(ctx->d_bface + ctx->boff[f] * 16, rows.data(), rows.size() * sizeof(double),
-                    hipMemcpyHostToDevice) != hipSuccess)
-        return fail(DGMI_EHIP, "dgmi_set_boundary: state upload failed");
+      for (int k = 0; k < ctx->bface_copies; ++k)
+        if (hipMemcpy(ctx->d_bface + (k * ctx->boff[6] + ctx->boff[f]) * 16, rows.data(), rows.size() * sizeof(double),
+                      hipMemcpyHostToDevice) != hipSuccess)
+          return fail(DGMI_EHIP, "dgmi_set_boundary: state upload failed");
     }
   }
   const int old = ctx->bc[direction];
@@ -1197,7 +1215,7 @@ dgmi_status dgmi_set_analytic_boundary(dgmi_ctx *ctx, int32_t direction, int32_t
   if (!params_host || nparams != 6) return fail(DGMI_EINVAL, "dgmi_set_analytic_boundary: 6 parameters expected");
   for (int k = 0; k < 6; ++k)
     if (!std::isfinite(params_host[k])) return fail(DGMI_EINVAL, "dgmi_set_analytic_boundary: non-finite parameter");
-  dgmi_status st = ensure_bface(ctx);
+  dgmi_status st = ensure_bface(ctx, 3);
   if (st != DGMI_OK) return st;
   for (int k = 0; k < 6; ++k) ctx->vortex[k] = params_host[k];
   const int old = ctx->bc[direction];
@@ -1368,7 +1386,7 @@ dgmi_status dg_step_ab3(dgmi_ctx *ctx, double *U, double *prim_inout, double dt,
     st = mixed_pass(ctx, 0, U, prim_inout, Ln, nullptr, nullptr, 0.0, 0.0, 0, s);
     if (st != DGMI_OK) return st;
   } else {
-    st = boundary_pass(ctx, ctx->time, s);
+    st = boundary_pass(ctx, &ctx->time, 1, s);
     if (st != DGMI_OK) return st;
     dgmi::RhsArgs a = rhs_args(ctx);
     a.U = U;

