@@ -73,6 +73,50 @@ __device__ __forceinline__ void load_node(const double *U, const double *Pr, int
   }
 }
 
+typedef __attribute__((address_space(4))) const double scalar_f64;
+
+// Doubles between the channels of a face's buffer: a lane per line reads and
+// writes with at most two lanes to a bank.
+constexpr int kChan = 72;
+
+// One direction of a tensor-product map on NCH channels of a face, a lane per
+// line: out[c][o + so r] = sum_i M[o][i] in[c][i + si r] in buf (channel stride
+// kChan), for r < nr lines per channel; input index i at stride sti, output o
+// at stride sto (and the line number at the other one).  M (row stride 8) is the
+// same for every lane and comes through the scalar cache, so that a line is
+// read once, NI values for NI NO multiply-adds.  The lines of all passes are
+// read before any is written.
+template <int NCH, int NI, int NO, int NR, bool FIRST>
+__device__ __forceinline__ void map_lines(double *buf, scalar_f64 *M) {
+  // FIRST: lines run along the first tangential direction (line r at NI r in,
+  // NO r out), else along the second (line r starts at r, stride NR)
+  constexpr int LINES = NCH * NR, PASSES = (LINES + 63) / 64;
+  double x[PASSES][NI];
+#pragma unroll
+  for (int p = 0; p < PASSES; ++p) {
+    const int t = (int)threadIdx.x + 64 * p, c = t / NR, r = t - NR * c;
+    if (t < LINES) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) x[p][i] = buf[c * kChan + (FIRST ? i + NI * r : r + NR * i)];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int o = 0; o < NO; ++o) {
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+      const int t = (int)threadIdx.x + 64 * p, c = t / NR, r = t - NR * c;
+      if (t < LINES) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) s += M[o * 8 + i] * x[p][i];
+        buf[c * kChan + (FIRST ? o + NO * r : r + NR * o)] = s;
+      }
+    }
+  }
+  __syncthreads();
+}
+
 }  // namespace
 
 
@@ -80,25 +124,19 @@ __device__ __forceinline__ void load_node(const double *U, const double *Pr, int
 // compile-time constant.
 template <int SYS, int FLUX, int NLO, int NMX>
 __device__ __forceinline__ void mortar_face(const MortarArgs &A, int64_t qhi, int64_t qlo, int64_t ohi, int64_t olo,
-                                            int d, int side_hi, double *buf, double *sI, double *sP) {
+                                            int d, int side_hi, double *buf) {
   constexpr int NV = SysTraits<SYS>::nv, NS = Interp<SYS>::ns;
   // channels interpolated to the mortar: the state, then the lower side's
   // nodal normal fluxes
   constexpr int NC = NS + NV;
   constexpr int nm = NMX + 1, nl = NLO + 1;
-  // one buffer serves every phase: a phase reads it into registers and
-  // writes its results back only after a barrier
-  double *const st = buf;  // lower side's state and F_h, [c][node]            (L, I1)
-  double *const t1 = buf;  // interpolated along a, [c][ma + nm ib]             (I1, I2)
-  double *const jm = buf;  // F*.n_lo - I F_h.n_lo at the mortar nodes, [v][m]  (I2, P1)
-  double *const g1 = buf;  // projection along a, [v][a + nl mb]               (P1, P2)
+  // one buffer [channel][kChan] serves every phase
   const int l = threadIdx.x;
   const int side_lo = 1 - side_hi;
   const double sgn_hi = side_hi ? 1.0 : -1.0, sgn_lo = -sgn_hi;
   const int64_t nn = A.nnodes;
   constexpr int tab = (NLO * 8 + NMX) * 64;
-  sI[l] = A.Itab[tab + l];  // I[ma][ia] (row stride 8)
-  sP[l] = A.Ptab[tab + l];  // P[a][ma]
+  scalar_f64 *I = (scalar_f64 *)(A.Itab + tab), *Pm = (scalar_f64 *)(A.Ptab + tab);  // I[ma][ia], P[a][ma]
 
   // the higher side's node of this lane's mortar position, loaded up front so
   // that its latency overlaps the lower side's loads
@@ -125,57 +163,32 @@ __device__ __forceinline__ void mortar_face(const MortarArgs &A, int64_t qhi, in
     load_node<SYS>(A.U, A.P, nn, q, A.gamma, u, P);
     double W = 1.0;
     if (SYS != kNE) W = fast_rcp(fast_sqrt(1.0 - (P.v[0] * P.v[0] + P.v[1] * P.v[1] + P.v[2] * P.v[2])));
-    st[l] = P.rho;
-    st[64 + l] = P.v[0] * W;
-    st[128 + l] = P.v[1] * W;
-    st[192 + l] = P.v[2] * W;
-    st[256 + l] = P.p;
+    buf[l] = P.rho;
+    buf[kChan + l] = P.v[0] * W;
+    buf[2 * kChan + l] = P.v[1] * W;
+    buf[3 * kChan + l] = P.v[2] * W;
+    buf[4 * kChan + l] = P.p;
     if (SYS == kMHD) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) st[(5 + c) * 64 + l] = u[5 + c];
+      for (int c = 0; c < 4; ++c) buf[(5 + c) * kChan + l] = u[5 + c];
     }
     double F[NV];
     flux_normal<SYS>(d, u, P, F);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) st[(NS + v) * 64 + l] = F[v];
+    for (int v = 0; v < NV; ++v) buf[(NS + v) * kChan + l] = F[v];
   }
   __syncthreads();
 
-  // I1: t1[c][ma + nm ib] = sum_ia I[ma][ia] st[c][ia + nl ib]
-  {
-    double acc[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) acc[c] = 0.0;
-    if (l < nm * nl) {
-      const int ma = l % nm, ib = l / nm;
-      #pragma unroll
-      for (int ia = 0; ia < nl; ++ia) {
-        const double w = sI[ma * 8 + ia];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) acc[c] += w * st[c * 64 + ia + nl * ib];
-      }
-    }
-    __syncthreads();
-    if (l < nm * nl) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) t1[c * 64 + l] = acc[c];
-    }
-  }
-  __syncthreads();
+  // I1, I2: the channels at the mortar nodes, one tangential direction at a time
+  map_lines<NC, nl, nm, nl, true>(buf, I);
+  map_lines<NC, nl, nm, nm, false>(buf, I);
 
-  // I2 + flux at the mortar node
+  // flux at the mortar node
   double jr[NV];
   if (l < nm * nm) {
-    const int ma = l % nm, mb = l / nm;
     double s[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) s[c] = 0.0;
-    #pragma unroll
-    for (int ib = 0; ib < nl; ++ib) {
-      const double w = sI[mb * 8 + ib];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) s[c] += w * t1[c * 64 + ma + nm * ib];
-    }
+    for (int c = 0; c < NC; ++c) s[c] = buf[c * kChan + l];
     double ul[NV], Fl[NV];
     Prim Pl;
     interp_to_state<SYS>(s, A.gamma, ul, Pl);
@@ -221,47 +234,17 @@ __device__ __forceinline__ void mortar_face(const MortarArgs &A, int64_t qhi, in
   __syncthreads();
   if (l < nm * nm) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) jm[v * 64 + l] = jr[v];
+    for (int v = 0; v < NV; ++v) buf[v * kChan + l] = jr[v];
   }
   __syncthreads();
 
-  // P1: g1[v][a + nl mb] = sum_ma P[a][ma] jm[v][ma + nm mb]
-  {
-    double acc[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) acc[v] = 0.0;
-    if (l < nl * nm) {
-      const int a = l % nl, mb = l / nl;
-      #pragma unroll
-      for (int ma = 0; ma < nm; ++ma) {
-        const double w = sP[a * 8 + ma];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) acc[v] += w * jm[v * 64 + ma + nm * mb];
-      }
-    }
-    __syncthreads();
-    if (l < nl * nm) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) g1[v * 64 + l] = acc[v];
-    }
-  }
-  __syncthreads();
-
-  // P2: lower side's lift term P (F*.n_lo - I F_h.n_lo) at node (a, b)
+  // P1, P2: lower side's lift term P (F*.n_lo - I F_h.n_lo) at its nodes
+  map_lines<NV, nm, nl, nm, true>(buf, Pm);
+  map_lines<NV, nm, nl, nl, false>(buf, Pm);
   if (l < nl * nl) {
-    const int a = l % nl, b = l / nl;
-    double g[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) g[v] = 0.0;
-    #pragma unroll
-    for (int mb = 0; mb < nm; ++mb) {
-      const double w = sP[b * 8 + mb];
-#pragma unroll
-      for (int v = 0; v < NV; ++v) g[v] += w * g1[v * 64 + a + nl * mb];
-    }
     double *out_lo = A.facebuf + olo + l;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) out_lo[v * nl * nl] = g[v];
+    for (int v = 0; v < NV; ++v) out_lo[v * nl * nl] = buf[v * kChan + l];
   }
 }
 
@@ -269,12 +252,17 @@ __device__ __forceinline__ void mortar_face(const MortarArgs &A, int64_t qhi, in
 // interpolation and projection one direction at a time):
 //   L  lanes k < (Nlo+1)^2 load the lower side's face nodes: interpolation
 //      state and normal fluxes F_h;
-//   I1 interpolate the state and F_h along the first tangential direction;
-//   I2 finish the interpolation at the mortar nodes; each mortar lane (which
-//      loaded its higher-side node at the start) forms F*.n, writes the
-//      higher side's lift term F*.n - F.n and keeps F*.n_lo - I F_h.n_lo;
+//   I1, I2 interpolate the state and F_h along each tangential direction; each
+//      mortar lane (which loaded its higher-side node at the start) forms
+//      F*.n, writes the higher side's lift term F*.n - F.n and keeps
+//      F*.n_lo - I F_h.n_lo;
 //   P1, P2 project that difference onto the lower side's nodes along each
 //      direction.
+// The maps run a lane per line with the matrix on the scalar side (map_lines).
+// (A lane per output node read every input value once per output from LDS: 230
+// LDS reads a face, which alone took 15 of the 24.8 us of the pass over 16^3
+// elements of degrees 2 to 7 (10,200 faces), at 140 VGPRs; now about 80 reads
+// and 71 VGPRs: a mixed RK3 step of three passes went from 186 to 171 us.)
 // Workgroups are mapped XCD-major (hardware block b runs on XCD b % 8 and
 // walks its own contiguous range of the face list), so that faces of nearby
 // elements, which share cache lines of the node blocks, share an L2.  The
@@ -283,8 +271,7 @@ __device__ __forceinline__ void mortar_face(const MortarArgs &A, int64_t qhi, in
 template <int SYS, int FLUX>
 __global__ void __launch_bounds__(64) mortar_kernel(const MortarArgs A) {
   constexpr int NC = Interp<SYS>::ns + SysTraits<SYS>::nv;
-  __shared__ double buf[NC * 64];
-  __shared__ double sI[64], sP[64];
+  __shared__ double buf[NC * kChan];
   const int64_t per = (A.nfaces + 7) >> 3;
   const int64_t t = (int64_t)(blockIdx.x & 7) * per + (int64_t)(blockIdx.x >> 3);
   if (t >= A.nfaces) return;
@@ -293,7 +280,7 @@ __global__ void __launch_bounds__(64) mortar_kernel(const MortarArgs A) {
   const int info = (int)fd[4];
   const int d = info & 3, side_hi = (info >> 2) & 1, Nm = (info >> 3) & 7, Nlo = (info >> 6) & 7;
 #define DGMI_MORTAR_CASE(LO, HI) \
-  case LO * 8 + HI: mortar_face<SYS, FLUX, LO, HI>(A, qhi, qlo, ohi, olo, d, side_hi, buf, sI, sP); break;
+  case LO * 8 + HI: mortar_face<SYS, FLUX, LO, HI>(A, qhi, qlo, ohi, olo, d, side_hi, buf); break;
   switch (Nlo * 8 + Nm) {
     DGMI_MORTAR_CASE(1, 2) DGMI_MORTAR_CASE(1, 3) DGMI_MORTAR_CASE(1, 4) DGMI_MORTAR_CASE(1, 5)
     DGMI_MORTAR_CASE(1, 6) DGMI_MORTAR_CASE(1, 7) DGMI_MORTAR_CASE(2, 3) DGMI_MORTAR_CASE(2, 4)
