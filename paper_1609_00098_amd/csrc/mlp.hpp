@@ -57,6 +57,47 @@ __host__ __device__ __forceinline__ void mlp_features(const double *u, double g,
   x[4] = (float)log(f0 / D);
 }
 
+// ln x of a positive double to FP32 accuracy (also below the FP32 range): the
+// hardware's log2 of the mantissa, plus the exponent.
+__device__ __forceinline__ float log_to_float(double x) {
+  const float m = (float)__builtin_amdgcn_frexp_mant(x);
+  return ((float)__builtin_amdgcn_frexp_exp(x) + __builtin_amdgcn_logf(m)) * 0.693147181f;
+}
+
+// ln(1 + s) for s >= 0, the rounding of 1 + s put back to first order.
+__device__ __forceinline__ float log1_fast(float s) {
+  const float t = 1.0f + s;
+  return fmaf(s - (t - 1.0f), __builtin_amdgcn_rcpf(t), __logf(t));
+}
+
+// The same features for the recovery's seed, from the hardware's FP32 logarithms,
+// roots and reciprocals (within an ulp or two of mlp_features' library calls,
+// which with its FP64 logarithm and divisions take about 500 instructions more
+// per point).
+template <int SYS>
+__device__ __forceinline__ void seed_features(const double *u, double g, float *x) {
+  const double D = u[0], tau = u[4];
+  const double S2 = u[1] * u[1] + u[2] * u[2] + u[3] * u[3];
+  double BB = 0.0, SB = 0.0, f0 = 0.0;
+  bool defined;
+  if (SYS == 2) {
+    BB = u[5] * u[5] + u[6] * u[6] + u[7] * u[7];
+    SB = u[1] * u[5] + u[2] * u[6] + u[3] * u[7];
+    double em, e;
+    defined = mhd_f0(u, g, &f0, &em, &e);
+  } else {
+    defined = pressure_function<SYS>(u, g, 0.0, &f0);
+  }
+  if (!defined || !(f0 > 0.0)) f0 = 1e-300 * D;
+  const float Df = (float)D, r = __builtin_amdgcn_rcpf(Df), iD = fmaf(fmaf(-Df, r, 1.0f), r, r);
+  const float Sa = __builtin_amdgcn_sqrtf((float)S2), Ba = __builtin_amdgcn_sqrtf((float)BB);
+  x[0] = __logf((float)tau * iD);
+  x[1] = log1_fast(Sa * iD);
+  x[2] = log1_fast((float)BB * iD);
+  x[3] = (float)SB * __builtin_amdgcn_rcpf(Sa * Ba + 1e-30f);
+  x[4] = log_to_float(f0 * fast_rcp(D));
+}
+
 // ---------------------------------------------------------------------
 // Inference on the matrix cores.  A wave evaluates 32 samples at a time with
 // both layers transposed, [units x inputs] x [inputs x samples] in 32 x 32
@@ -105,7 +146,7 @@ struct MlpNet {  // per block: the weights as the products read them
   bf16x8_t w2[2][4][64][3];
   alignas(16) float b2[kH], w3[kH];
   float w1[kH][kIn + 1];  // W1, and b1 as the sixth column
-  float b3, mu[kIn], sd[kIn], ymu, ysd;
+  float b3, mu[kIn], sd[kIn], isd[kIn], isl[kIn], ymu, ysd;  // 1 / sd = isd + isl
 };
 
 __device__ __forceinline__ void mlp_net_load(const float *p, MlpNet *s) {
@@ -130,6 +171,9 @@ __device__ __forceinline__ void mlp_net_load(const float *p, MlpNet *s) {
   if (threadIdx.x < kIn) {
     s->mu[threadIdx.x] = p[kOffMu + threadIdx.x];
     s->sd[threadIdx.x] = p[kOffSd + threadIdx.x];
+    const double isd = 1.0 / (double)p[kOffSd + threadIdx.x];
+    s->isd[threadIdx.x] = (float)isd;
+    s->isl[threadIdx.x] = (float)(isd - (double)(float)isd);
   }
   if (threadIdx.x == 0) {
     s->b3 = p[kOffB3];
@@ -213,9 +257,12 @@ template <int SYS>
 __device__ __forceinline__ double mlp_seed_wave(const MlpNet *s, const double *u, double g) {
   const bool lo = (threadIdx.x & 63) < 32;
   float x[kIn];
-  mlp_features<SYS>(u, g, x);
+  seed_features<SYS>(u, g, x);
 #pragma unroll
-  for (int i = 0; i < kIn; ++i) x[i] = (x[i] - s->mu[i]) / s->sd[i];
+  for (int i = 0; i < kIn; ++i) {
+    const float c = x[i] - s->mu[i];
+    x[i] = fmaf(c, s->isl[i], c * s->isd[i]);
+  }
   // an input pair (k, k + 1): each half-wave needs its own row of the pair
   // for both passes, the other half holds it for one of them
   const float o0 = __shfl_xor(lo ? x[1] : x[0], 32), o1 = __shfl_xor(lo ? x[3] : x[2], 32), o2 = __shfl_xor(x[4], 32);
@@ -228,8 +275,12 @@ __device__ __forceinline__ double mlp_seed_wave(const MlpNet *s, const double *u
     if (own) y = yp;
   }
   y = y * s->ysd + s->ymu;
-  // the seed needs no more than FP32 (the FP64 iteration decides the result)
-  return u[0] * (double)__expf(y);
+  // the seed needs no more than FP32 (the FP64 iteration decides the result):
+  // exp y = 2^t (1 + r ln 2), r the rounding of t = y log2 e
+  const float t = y * 1.44269504f;
+  const float r = fmaf(y, 1.44269504f, -t) + y * 1.92596299e-8f;
+  const float e = __builtin_amdgcn_exp2f(t);
+  return u[0] * (double)fmaf(e, r * 0.693147181f, e);
 }
 
 }  // namespace dgmi

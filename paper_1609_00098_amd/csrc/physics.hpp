@@ -12,6 +12,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #define DG_HD __host__ __device__ __forceinline__
 
 namespace dgmi {
@@ -61,6 +63,24 @@ DG_HD double fast_sqrt(double x) {
   return x > 0.0 ? g : 0.0;
 #else
   return x > 0.0 ? sqrt(x) : 0.0;
+#endif
+}
+
+// sqrt(x) and 1 / sqrt(x) for x > 0 from the same estimate.
+DG_HD void fast_sqrt_rsq(double x, double &g, double &ig) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const double r = __builtin_amdgcn_rsq(x);
+  g = x * r;
+  double h = 0.5 * r;
+  const double e = fma(-h, g, 0.5);
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  const double d = fma(-g, g, x);
+  g = fma(d, h, g);
+  ig = h + h;
+#else
+  g = sqrt(x);
+  ig = 1.0 / g;
 #endif
 }
 
@@ -548,6 +568,37 @@ DG_HD double cubic_top_root(double e, double d, double x0) {
   return x;
 }
 
+// The same root for the recovery to a tolerance, in fewer iterations.  (The
+// polished recovery and its last digits stay with cubic_top_root: its step tests
+// read f's rounding, and with this root 4% of its points took another number of
+// steps and the primitives were 7% further from exact, at 8.1e-14.)  Without a starting value
+// (x0 <= 0) it starts from the closed form y = 1/3 + 2/3 cos(2/3 acos s),
+// s = sqrt(1 - 27/4 d / e^3), x = e y, as a polynomial in s (within 9.2e-7, its
+// interpolant at Chebyshev points) raised by 1e-6, so that Newton still descends
+// from above; and it stops
+// as soon as the error the last step leaves, (3x - e) / (x (3x - 2e)) dx^2, is
+// below 1e-16 x, instead of after a step of rounding size.
+DG_HD double cubic_root_near(double e, double d, double x0) {
+  double x = x0;
+  if (!(x0 > 0.0)) {
+    const double ie = fast_rcp(e);
+    const double q = 1.0 - 6.75 * (d * ie * ie * ie);
+    const double s = fast_sqrt(q);
+    x = e * fma(s, fma(s, fma(s, fma(s, fma(s, 0.002747202199448869, -0.01274788569041144), 0.03175633797436024), -0.07325630656007719), 0.3848336033384197), 0.6666685820054394);
+  }
+#pragma unroll 1
+  for (int k = 0; k < 40; ++k) {
+    const double dq = x * (3.0 * x - 2.0 * e);
+    if (!(dq > 0.0)) return -1.0;
+    const double dx = (x * x * (x - e) + d) * fast_rcp(dq);
+    const double left = dx * dx * (3.0 * x - e);
+    const double lim = 1.0e-16 * x * dq;
+    x -= dx;
+    if (left <= lim) break;
+  }
+  return x;
+}
+
 // Pressure function f(p) = (g-1) rho eps(p) - p of a conserved state at one
 // trial pressure; returns false where the map is undefined (no admissible
 // root of the magnetic cubic, z <= 0 or v^2 >= 1).
@@ -641,12 +692,62 @@ DG_HD bool fix_conserved(double *u, double g, double D_min, double tau_min) {
   return true;
 }
 
+// The root at coefficient e, from the one (em_prev, e_prev) of a nearby pressure
+// if there is one (em_prev > 0): the root moves at least as much as e does.
+DG_HD double mhd_start(double e, double em_prev, double e_prev) {
+  return fmin(fmax(em_prev + (e - e_prev), 2.0 * e / 3.0 + 1e-3 * e), e);
+}
+DG_HD double mhd_root_near(double e, double d, double em_prev, double e_prev) {
+  return cubic_root_near(e, d, em_prev > 0.0 ? mhd_start(e, em_prev, e_prev) : -1.0);
+}
+DG_HD double mhd_root_polished(double e, double d, double em_prev, double e_prev) {
+  return cubic_top_root(e, d, em_prev > 0.0 ? mhd_start(e, em_prev, e_prev) : e);
+}
+
+// f(0), the seed of recoveries to a tolerance (f(0) mode, the network's feature):
+// the pressure function at zero
+// pressure, with the cubic's root em and coefficient e there.  False where it is
+// undefined (as pressure_function).
+DG_HD bool mhd_f0(const double *u, double g, double *f, double *em_out, double *e_out) {
+  const double D = u[0], tau = u[4];
+  const double S2 = u[1] * u[1] + u[2] * u[2] + u[3] * u[3];
+  const double BB = u[5] * u[5] + u[6] * u[6] + u[7] * u[7];
+  const double T = u[1] * u[5] + u[2] * u[6] + u[3] * u[7];
+  double dc = 0.5 * (BB * S2 - T * T);
+  dc = dc > 0.0 ? dc : 0.0;
+  const double e = tau + D + 0.5 * BB;
+  if (!(e > 0.0)) return false;
+  const double em = cubic_root_near(e, dc, -1.0), z = em - BB;
+  if (!(em > 0.0) || !(z > 0.0)) return false;
+  const double r = fast_rcp(z * em), Tz = T * (em * r), iem = z * r;
+  const double uu = 1.0 - (S2 + Tz * Tz * (z + em)) * (iem * iem);
+  if (!(uu > 0.0)) return false;
+  *f = (g - 1.0) * (z * uu - D * fast_sqrt(uu));
+  *em_out = em;
+  *e_out = e;
+  return true;
+}
+
 // Recovery of one point.  p0: initial pressure (outside the bracket => the
 // bracket's upper end).  tol > 0: stop when the backward residual
 // |f| W^2 / ((g-1) E) <= 0.99 tol at the evaluated pressure; tol <= 0:
 // iterate Newton until the step is below 1e-14 p (rounding level).
-template <int SYS>
-DG_HD C2PResult recover(const double *u, double g, double p0, double tol, int maxit, bool poly = false) {
+// em0, e0 (MHD): a root of the cubic at another pressure and its coefficient,
+// which start the first evaluation's (em0 <= 0: none).  TOL: tolerance mode
+// (tol > 0), else polish mode.
+//
+// The iteration runs first without the record of the smallest |f| (a last
+// resort that a converged point never needs), for up to kPlainIters
+// evaluations; a point that has not converged by then starts over with it and
+// all maxit, so that its result is that of one tracked run.  For SRMHD in
+// tolerance mode, with the cubic's start and stop above, shared reciprocals and
+// the modes compiled apart, 1,284 -> 886 vector instructions a point (f(0) seed),
+// 1,002 -> 755 us for 2.5e7 points: vector issue bound it at 83%, 77% now.
+constexpr int kPlainIters = 16;
+
+template <int SYS, bool TOL>
+DG_HD C2PResult recover_as(const double *u, double g, double p0, double tol, int maxit, bool poly, double em0,
+                           double e0) {
   C2PResult R;
   R.iters = 0;
   R.ok = 0;
@@ -668,131 +769,153 @@ DG_HD C2PResult recover(const double *u, double g, double p0, double tol, int ma
     dcub = 0.5 * (BB * S2 - T * T);
     dcub = dcub > 0.0 ? dcub : 0.0;
   }
-  double lo = 0.0;
-  double hi = gm1 * (tau - 0.5 * BB);
+  const double top = gm1 * (tau - 0.5 * BB);  // the bracket's upper end
   R.P.rho = D;
   R.P.v[0] = R.P.v[1] = R.P.v[2] = 0.0;
-  R.P.p = hi;
-  if (!(D > 0.0) || !(hi > 0.0) || !(E > 0.0)) {
-    if (SYS == kMHD) R.z = -(D + g / gm1 * hi);
+  R.P.p = top;
+  if (!(D > 0.0) || !(top > 0.0) || !(E > 0.0)) {
+    if (SYS == kMHD) R.z = -(D + g / gm1 * top);
     return R;
   }
   if (SYS == kSR && !(E * E - S2 > D * D)) return R;  // f(0) <= 0: no physical state
-  const double Sabs = fast_sqrt(S2);
-  double p = (p0 > lo && p0 < hi) ? p0 : hi;
-  double em_prev = -1.0, e_prev = 0.0;
-  double z = 0.0, em = 0.0, W = 1.0;
-  double prev_step = 1e300;
-  bool last_small = false;
-  int conv = 0;
+  const double Sabs = SYS == kSR ? fast_sqrt(S2) : 0.0;
+  const double pstart = (p0 > 0.0 && p0 < top) ? p0 : top;
+  double p = pstart, em_prev = em0, e_prev = e0;
   // the evaluated pressure with the smallest |f|, and whether that |f| lies
   // within the rounding of f's terms (a last resort when the iteration runs
   // out: for an extreme Lorentz factor 1 - v^2 cancels and f carries noise
   // far above 1e-14 p, so neither the step tests nor the bracket settle)
-  double p_best = p, f_best = 1e300;
+  double p_best = p;
   bool best_at_floor = false;
+  auto iterate = [&](auto track_, int cap) __attribute__((always_inline)) {
+    constexpr bool track = decltype(track_)::value;
+    double lo = 0.0, hi = top;
+    double f_best = 1e300, prev_step = 1e300;
+    bool last_small = false;
+    p = p_best = pstart;
+    em_prev = em0;
+    e_prev = e0;
 #pragma unroll 1
-  for (int it = 1; it <= maxit; ++it) {
-    R.iters = it;
-    int valid = 1;
-    double v2, e = 0.0;
-    double iz = 0.0, t = 0.0, uu = 0.0, sqw = 0.0;
-    if (SYS == kSR) {
-      // q = z^2 - S^2 = z^2 / W^2 without the cancellation of 1 - v^2; one
-      // division t = 1/(z sqrt(q)) gives 1/z, W and sqrt(1 - v^2)
-      z = tau + D + p;
-      const double q = (z - Sabs) * (z + Sabs);
-      const double sqq = fast_sqrt(q);
-      t = fast_rcp(z * sqq);
-      iz = sqq * t;
-      v2 = S2 * iz * iz;
-      uu = q * iz * iz;
-      sqw = q * t;
-      W = z * z * t;
-    } else {
-      e = E + p + 0.5 * BB;
-      const double x0 = (em_prev > 0.0) ? fmax(em_prev + (e - e_prev), 2.0 * e / 3.0 + 1e-3 * e) : e;
-      em = cubic_top_root(e, dcub, fmin(x0, e));
-      z = em - BB;
-      valid = (em > 0.0) && (z > 0.0);
-      v2 = valid ? (S2 * z * z + T * T * (z + em)) * fast_rcp(z * z * em * em) : 1.0;
-      if (valid) { em_prev = em; e_prev = e; }
-    }
-    valid = valid && (v2 < 1.0);
-    if (!valid) {  // pressure below the domain of the map: raise it
-      lo = p;
-      const double pn = 0.5 * (lo + hi);
-      if (!(pn > lo && pn < hi)) break;
+    for (int it = 1; it <= cap; ++it) {
+      R.iters = it;
+      int valid = 1;
+      double v2, e = 0.0, z, em = 0.0, W;
+      double iz = 0.0, t = 0.0, uu = 0.0, sqw = 0.0, iem = 0.0, Tz = 0.0;
+      if (SYS == kSR) {
+        // q = z^2 - S^2 = z^2 / W^2 without the cancellation of 1 - v^2; one
+        // division t = 1/(z sqrt(q)) gives 1/z, W and sqrt(1 - v^2)
+        z = tau + D + p;
+        const double q = (z - Sabs) * (z + Sabs);
+        const double sqq = fast_sqrt(q);
+        t = fast_rcp(z * sqq);
+        iz = sqq * t;
+        v2 = S2 * iz * iz;
+        uu = q * iz * iz;
+        sqw = q * t;
+        W = z * z * t;
+      } else {
+        e = E + p + 0.5 * BB;
+        if (TOL) {
+          em = mhd_root_near(e, dcub, em_prev, e_prev);
+          z = em - BB;
+          valid = (em > 0.0) && (z > 0.0);
+          // one reciprocal 1 / (z em) gives both; T / z = B.v
+          const double r = fast_rcp(z * em);
+          iz = em * r;
+          iem = z * r;
+          Tz = T * iz;
+          v2 = valid ? (S2 + Tz * Tz * (z + em)) * (iem * iem) : 1.0;
+        } else {
+          em = mhd_root_polished(e, dcub, em_prev, e_prev);
+          z = em - BB;
+          valid = (em > 0.0) && (z > 0.0);
+          v2 = valid ? (S2 * z * z + T * T * (z + em)) * fast_rcp(z * z * em * em) : 1.0;
+        }
+        if (valid) { em_prev = em; e_prev = e; }
+      }
+      valid = valid && (v2 < 1.0);
+      if (!valid) {  // pressure below the domain of the map: raise it
+        lo = p;
+        const double pn = 0.5 * (lo + hi);
+        if (!(pn > lo && pn < hi)) return 0;
+        p = pn;
+        continue;
+      }
+      if (SYS == kMHD) {
+        uu = 1.0 - v2;  // 1/W^2
+        if (TOL) {
+          fast_sqrt_rsq(uu, sqw, W);
+        } else {
+          sqw = fast_sqrt(uu);
+          W = fast_rcp(sqw);
+        }
+      }
+      const double rho_eps = z * uu - D * sqw - p;
+      const double f = gm1 * rho_eps - p;
+      if (track && fabs(f) < f_best) {
+        f_best = fabs(f);
+        p_best = p;
+        // |f| <= 32 eps (g-1) (z + D / sqrt(1 - v^2)), without the division
+        best_at_floor = f_best * sqw <= 7.105427357601002e-15 * gm1 * (z * sqw + D);
+      }
+      // |f| W^2 / ((g-1) E) is the backward residual |tau(P) - tau| / E of the
+      // primitives at p to first order (and bounds the momentum's); 1% of
+      // margin covers the rounding of the residual itself, a few 1e-14 of E
+      // for strongly magnetised states at large W
+      if (TOL && fabs(f) * W * W <= 0.99 * tol * gm1 * E) return 1;
+      if (f > 0.0) lo = p; else hi = p;
+      // the Newton step is num / df: f and f', in tolerance mode for MHD both
+      // times 3 em - 2 e, the denominator of d em / dp = em / (3 em - 2 e)
+      double df, num = f;
+      if (SYS == kSR) {
+        df = gm1 * v2 * (1.0 - D * z * t) - 1.0;  // W / z = z t
+      } else if (!TOL) {
+        const double dem = em * fast_rcp(3.0 * em - 2.0 * e);  // d eps_m / dp
+        const double iz = fast_rcp(z), iem = fast_rcp(em);
+        const double dv2 = -2.0 * dem * (S2 * iem * iem * iem +
+                                         T * T * (iz * iz * iem * iem + iz * iem * iem * iem + iz * iz * iz * iem));
+        const double drho_eps = dem * uu - dv2 * (z - 0.5 * D * W) - 1.0;
+        df = gm1 * drho_eps - 1.0;
+      } else {
+        const double den = 3.0 * em - 2.0 * e;
+        const double dv2 = -2.0 * em * iem * (S2 * iem * iem + Tz * Tz * (iem + z * (iem * iem) + iz));
+        df = gm1 * (em * uu - dv2 * (z - 0.5 * D * W) - den) - den;
+        num = f * den;
+      }
+      if (f == 0.0) return 1;  // exact root
+      double pn = p - num * step_rcp(df);
+      // closed bracket: at the root f is rounding noise and the proposal can
+      // land on the end point just set to p
+      const bool newton = (pn >= lo && pn <= hi);
+      // Right after a Newton step below 1e-9 p the iterate sits at the rounding
+      // floor of f; a proposal outside the bracket is then noise.
+      if (!TOL && !newton && last_small) return 1;
+      if (!newton) pn = 0.5 * (lo + hi);
+      const double step = fabs(pn - p);
       p = pn;
-      continue;
+      if (!TOL) {
+        // Polishing.  A bracket below 1e-14 p pins the root.  Otherwise only a
+        // genuine Newton step may end the iteration: Newton converges
+        // quadratically, so after a step below 1e-11 p the new iterate is
+        // accurate to rounding, and a Newton step that no longer halves (once
+        // below 1e-9 p) marks the rounding floor of f.  (A bisection step can be
+        // small without the iterate being close.)
+        if (hi - lo <= 1e-14 * p ||
+            (newton && (step <= 1e-11 * p || (step <= 1e-9 * p && step >= 0.5 * prev_step))))
+          return 1;
+        prev_step = newton ? step : 1e300;
+        last_small = newton && step <= 1e-9 * p;
+      }
     }
-    if (SYS == kMHD) {
-      uu = 1.0 - v2;  // 1/W^2
-      sqw = fast_sqrt(uu);
-      W = fast_rcp(sqw);
-    }
-    const double rho_eps = z * uu - D * sqw - p;
-    const double f = gm1 * rho_eps - p;
-    if (fabs(f) < f_best) {
-      f_best = fabs(f);
-      p_best = p;
-      // |f| <= 32 eps (g-1) (z + D / sqrt(1 - v^2)), without the division
-      best_at_floor = f_best * sqw <= 7.105427357601002e-15 * gm1 * (z * sqw + D);
-    }
-    // |f| W^2 / ((g-1) E) is the backward residual |tau(P) - tau| / E of the
-    // primitives at p to first order (and bounds the momentum's); 1% of
-    // margin covers the rounding of the residual itself, a few 1e-14 of E
-    // for strongly magnetised states at large W
-    if (tol > 0.0 && fabs(f) * W * W <= 0.99 * tol * gm1 * E) {
+    return 0;
+  };
+  int conv = iterate(std::false_type{}, maxit < kPlainIters ? maxit : kPlainIters);
+  if (!conv) {
+    conv = iterate(std::true_type{}, maxit);
+    if (!conv && !TOL && best_at_floor) {
+      p = p_best;
       conv = 1;
-      break;
     }
-    if (f > 0.0) lo = p; else hi = p;
-    double df;
-    if (SYS == kSR) {
-      df = gm1 * v2 * (1.0 - D * z * t) - 1.0;  // W / z = z t
-    } else {
-      const double dem = em * fast_rcp(3.0 * em - 2.0 * e);  // d eps_m / dp
-      const double iz = fast_rcp(z), iem = fast_rcp(em);
-      const double dv2 = -2.0 * dem * (S2 * iem * iem * iem +
-                                       T * T * (iz * iz * iem * iem + iz * iem * iem * iem + iz * iz * iz * iem));
-      const double drho_eps = dem * uu - dv2 * (z - 0.5 * D * W) - 1.0;
-      df = gm1 * drho_eps - 1.0;
-    }
-    if (f == 0.0) {  // exact root
-      conv = 1;
-      break;
-    }
-    double pn = p - f * step_rcp(df);
-    // closed bracket: at the root f is rounding noise and the proposal can
-    // land on the end point just set to p
-    const bool newton = (pn >= lo && pn <= hi);
-    // Right after a Newton step below 1e-9 p the iterate sits at the rounding
-    // floor of f; a proposal outside the bracket is then noise.
-    if (tol <= 0.0 && !newton && last_small) {
-      conv = 1;
-      break;
-    }
-    if (!newton) pn = 0.5 * (lo + hi);
-    const double step = fabs(pn - p);
-    p = pn;
-    // Polishing.  A bracket below 1e-14 p pins the root.  Otherwise only a
-    // genuine Newton step may end the iteration: Newton converges
-    // quadratically, so after a step below 1e-11 p the new iterate is
-    // accurate to rounding, and a Newton step that no longer halves (once
-    // below 1e-9 p) marks the rounding floor of f.  (A bisection step can be
-    // small without the iterate being close.)
-    if (tol <= 0.0 && (hi - lo <= 1e-14 * p ||
-                       (newton && (step <= 1e-11 * p || (step <= 1e-9 * p && step >= 0.5 * prev_step))))) {
-      conv = 1;
-      break;
-    }
-    prev_step = newton ? step : 1e300;
-    last_small = newton && step <= 1e-9 * p;
-  }
-  if (!conv && tol <= 0.0 && best_at_floor) {
-    p = p_best;
-    conv = 1;
   }
   // primitives at the final pressure (as prims_at_pressure forms them, with
   // |S| from above); rho > 0 holds exactly when z > |S|, i.e. v^2 < 1
@@ -807,26 +930,35 @@ DG_HD C2PResult recover(const double *u, double g, double p0, double tol, int ma
     R.ok = conv && (zf > 0.0) && (p > 0.0) && (R.P.rho > 0.0);
     return R;
   }
-  double v2;
-  double rho_w = 0.0;  // sqrt(1 - v^2)
-  {
-    const double e = E + p + 0.5 * BB;
-    const double x0 = (em_prev > 0.0) ? fmax(em_prev + (e - e_prev), 2.0 * e / 3.0 + 1e-3 * e) : e;
-    em = cubic_top_root(e, dcub, fmin(x0, e));
-    z = em - BB;
-    R.z = z;
-    const double Tz = T * fast_rcp(z), iem = fast_rcp(em);
-    R.P.v[0] = (S0 + Tz * u[5]) * iem;
-    R.P.v[1] = (S1 + Tz * u[6]) * iem;
-    R.P.v[2] = (S2c + Tz * u[7]) * iem;
-    v2 = sq(R.P.v[0]) + sq(R.P.v[1]) + sq(R.P.v[2]);
-    conv = conv && (em > 0.0) && (z > 0.0);
+  // (in tolerance mode a converged pressure is one that was evaluated)
+  const double e = E + p + 0.5 * BB;
+  const double em = !TOL ? mhd_root_polished(e, dcub, em_prev, e_prev)
+                         : (conv ? em_prev : mhd_root_near(e, dcub, em_prev, e_prev));
+  const double z = em - BB;
+  R.z = z;
+  double Tz, iem;
+  if (TOL) {
+    const double r = fast_rcp(z * em);
+    Tz = T * (em * r);
+    iem = z * r;
+  } else {
+    Tz = T * fast_rcp(z);
+    iem = fast_rcp(em);
   }
+  R.P.v[0] = (S0 + Tz * u[5]) * iem;
+  R.P.v[1] = (S1 + Tz * u[6]) * iem;
+  R.P.v[2] = (S2c + Tz * u[7]) * iem;
+  const double v2 = sq(R.P.v[0]) + sq(R.P.v[1]) + sq(R.P.v[2]);
   R.P.p = p;
-  if (SYS == kMHD) rho_w = fast_sqrt(1.0 - v2);
-  R.P.rho = D * rho_w;
-  R.ok = conv && (v2 < 1.0) && (p > 0.0) && (R.P.rho > 0.0);
+  R.P.rho = D * fast_sqrt(1.0 - v2);
+  R.ok = conv && (em > 0.0) && (z > 0.0) && (v2 < 1.0) && (p > 0.0) && (R.P.rho > 0.0);
   return R;
+}
+
+template <int SYS>
+DG_HD C2PResult recover(const double *u, double g, double p0, double tol, int maxit, bool poly = false) {
+  return tol > 0.0 ? recover_as<SYS, true>(u, g, p0, tol, maxit, poly, -1.0, 0.0)
+                   : recover_as<SYS, false>(u, g, p0, tol, maxit, poly, -1.0, 0.0);
 }
 
 }  // namespace dgmi

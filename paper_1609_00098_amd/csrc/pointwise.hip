@@ -6,7 +6,7 @@
 
 namespace dgmi {
 
-template <int SYS, int GUESS>
+template <int SYS, int GUESS, bool TOL>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GUESS == 2 ? 4 : 1))) con2prim_kernel(const C2PArgs A) {
   constexpr int NV = SysTraits<SYS>::nv;
   const int64_t n = A.n;
@@ -35,6 +35,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GUESS 
       u[4] = 1.0;
     }
     double p0 = -1.0;
+    double em0 = -1.0, e0 = 0.0;  // MHD, f(0) seed to a tolerance: the cubic's root at zero pressure
     int extra = 0;  // pressure-function evaluations spent on the seed
     if (GUESS == 0 && valid) p0 = A.prim[4 * n + q];
     if (GUESS == 2) {
@@ -53,11 +54,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GUESS 
       // from above for the states of interest (taken if it lies inside the
       // bracket; the recovery falls back to the bracket's top otherwise)
       double f0 = 0.0;
-      if (pressure_function<SYS>(u, A.gamma, 0.0, &f0) && f0 > 0.0) p0 = f0;
+      const bool defined = SYS == kMHD && TOL ? mhd_f0(u, A.gamma, &f0, &em0, &e0)
+                                              : pressure_function<SYS>(u, A.gamma, 0.0, &f0);
+      if (defined && f0 > 0.0) p0 = f0;
       extra = 1;
     }
     if (!valid) continue;
-    C2PResult R = recover<SYS>(u, A.gamma, p0, A.tol, 100, A.poly);
+    C2PResult R = recover_as<SYS, TOL>(u, A.gamma, p0, A.tol, 100, A.poly, em0, e0);
     R.iters += extra;
     if (SYS == kMHD) {
       A.prim[q] = R.P.rho;
@@ -93,7 +96,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GUESS 
 // VGPRs, seven waves per SIMD; SRMHD's longer recovery keeps one point per
 // thread, where the second point's registers cost more occupancy than the
 // overlap gains).
-template <int SYS, int GUESS>
+template <int SYS, int GUESS, bool TOL>
 __global__ void __launch_bounds__(256) con2prim2_kernel(const C2PArgs A) {
   static_assert(SYS != kMHD && GUESS <= 1, "NE / SR, input or bracket seed");
   constexpr int NV = SysTraits<SYS>::nv;
@@ -115,7 +118,7 @@ __global__ void __launch_bounds__(256) con2prim2_kernel(const C2PArgs A) {
     for (int j = 0; j < 2; ++j) {
       const int64_t q = qq[j];
       if (q >= n) continue;
-      C2PResult R = recover<SYS>(u[j], A.gamma, p0[j], A.tol, 100, A.poly);
+      C2PResult R = recover_as<SYS, TOL>(u[j], A.gamma, p0[j], A.tol, 100, A.poly, -1.0, 0.0);
       // (the operators rebuild rho and v from U and p: streamed, as above)
       __builtin_nontemporal_store(R.P.rho, &A.prim[q]);
       __builtin_nontemporal_store(R.P.v[0], &A.prim[n + q]);
@@ -136,7 +139,8 @@ __global__ void __launch_bounds__(256) con2prim2_kernel(const C2PArgs A) {
   }
 }
 
-template <int SYS>
+// TOL: tolerance mode (a.tol > 0) or polishing, compiled apart.
+template <int SYS, bool TOL>
 static hipError_t c2p_sys(int guess, const C2PArgs &a, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
   const int64_t blocks_needed = (a.n + 255) / 256;
@@ -145,34 +149,34 @@ static hipError_t c2p_sys(int guess, const C2PArgs &a, hipStream_t s) {
   const int grid2 = (int)(blocks2 < 65536 ? blocks2 : 65536);
   if constexpr (SYS != kMHD) {
     if (guess == 0 || guess == 1) {
-      if (guess == 0) hipLaunchKernelGGL((con2prim2_kernel<SYS, 0>), dim3(grid2), dim3(256), 0, s, a);
-      else hipLaunchKernelGGL((con2prim2_kernel<SYS, 1>), dim3(grid2), dim3(256), 0, s, a);
+      if (guess == 0) hipLaunchKernelGGL((con2prim2_kernel<SYS, 0, TOL>), dim3(grid2), dim3(256), 0, s, a);
+      else hipLaunchKernelGGL((con2prim2_kernel<SYS, 1, TOL>), dim3(grid2), dim3(256), 0, s, a);
       return hipGetLastError();
     }
+  } else {
+    if (guess == 0) hipLaunchKernelGGL((con2prim_kernel<SYS, 0, TOL>), dim3(grid), dim3(256), 0, s, a);
+    if (guess == 1) hipLaunchKernelGGL((con2prim_kernel<SYS, 1, TOL>), dim3(grid), dim3(256), 0, s, a);
   }
-  switch (guess) {
-    case 0: hipLaunchKernelGGL((con2prim_kernel<SYS, 0>), dim3(grid), dim3(256), 0, s, a); break;
-    case 1: hipLaunchKernelGGL((con2prim_kernel<SYS, 1>), dim3(grid), dim3(256), 0, s, a); break;
-    case 2:
-      if (SYS == kNE) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((con2prim_kernel<SYS, 2>), dim3(grid), dim3(256), 0, s, a);
-      break;
-    case 3:
-      if (SYS == kNE) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((con2prim_kernel<SYS, 3>), dim3(grid), dim3(256), 0, s, a);
-      break;
-    default: return hipErrorInvalidValue;
+  if constexpr (SYS != kNE) {
+    if (guess == 2) hipLaunchKernelGGL((con2prim_kernel<SYS, 2, TOL>), dim3(grid), dim3(256), 0, s, a);
+    if (guess == 3) hipLaunchKernelGGL((con2prim_kernel<SYS, 3, TOL>), dim3(grid), dim3(256), 0, s, a);
   }
+  if (guess < 0 || guess > (SYS == kNE ? 1 : 3)) return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_con2prim(int sys, int guess, const C2PArgs &a, hipStream_t s) {
+template <bool TOL>
+static hipError_t c2p_tol(int sys, int guess, const C2PArgs &a, hipStream_t s) {
   switch (sys) {
-    case kNE: return c2p_sys<kNE>(guess >= 2 ? 1 : guess, a, s);
-    case kSR: return c2p_sys<kSR>(guess, a, s);
-    case kMHD: return c2p_sys<kMHD>(guess, a, s);
+    case kNE: return c2p_sys<kNE, TOL>(guess >= 2 ? 1 : guess, a, s);
+    case kSR: return c2p_sys<kSR, TOL>(guess, a, s);
+    case kMHD: return c2p_sys<kMHD, TOL>(guess, a, s);
   }
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_con2prim(int sys, int guess, const C2PArgs &a, hipStream_t s) {
+  return a.tol > 0.0 ? c2p_tol<true>(sys, guess, a, s) : c2p_tol<false>(sys, guess, a, s);
 }
 
 template <int SYS>
