@@ -162,6 +162,7 @@ __device__ __forceinline__ void load_node(const double *U, const double *Pr, int
 // scalar cache.
 typedef __attribute__((address_space(4))) const int64_t scalar_i64;
 typedef __attribute__((address_space(4))) const int32_t scalar_i32;
+typedef __attribute__((address_space(4))) const double scalar_f64;
 
 // The work of one workgroup on element group grp, with BT threads and the
 // LDS block smem (the kernels below choose grp and provide both).
@@ -547,7 +548,19 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
     P.rho = 1.0; P.v[0] = P.v[1] = P.v[2] = 0.0; P.p = 1.0;
   }
 
-  // ---- volume term, one direction at a time
+  // ---- volume term, one direction at a time: every node's flux into the
+  // buffer, then its derivative.  Where a lane per line covers the workgroup's
+  // lines in one round, it reads its line once, contracts it with D (the same
+  // for all lanes, through the scalar cache) and writes it back in place for
+  // the nodes: 20 LDS accesses per direction at degree 4 instead of the 35 of a
+  // lane per node, each reading its whole pencil, which took 41 us of LDS time
+  // of the SR operator's 112 us (32^3 elements of degree 4); 99.5 us now.  With
+  // a second, partly filled round the lane per node is faster: SRMHD degree 3,
+  // 288 lines on 192 threads, 3.92 against 3.99 ms a step; SR degree 3, 320 on
+  // 256, 112 against 124 us.
+  constexpr int LINES = EPB * NV * NF;
+  constexpr bool BY_LINE = LINES <= BT;
+  scalar_f64 *const Dm = (scalar_f64 *)A.Dmat;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     if (active) {
@@ -557,28 +570,56 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
       for (int v = 0; v < NV; ++v) mybuf[v * NPE + a] = F[v];
     }
     __syncthreads();
-    if (active) {
-      const int idx = sel3i(d, ci, cj, ck);
-      const int stride = sel3i(d, 1, NP, NF);
-      int base = a - idx * stride;
-      // keep the pencil's first node opaque, so that every read below is
-      // one address plus a constant offset (the compiler would otherwise
-      // re-derive each node's address from idx)
-      asm volatile("" : "+v"(base));
-      const double *pen = mybuf + base;
-      const double scale = sel3(d, A.scale[0], A.scale[1], A.scale[2]);
-      double Drow[NP];
+    if constexpr (BY_LINE) {
+      const int stride = d == 0 ? 1 : (d == 1 ? NP : NF);
+      if (tid < LINES) {
+        const int b = tid / NF, r = tid - b * NF;  // block of (element, variable), line in it
+        const int el = b / NV, v = b - el * NV;
+        const int first = d == 0 ? NP * r : (d == 1 ? (r / NP) * (NF - NP) + r : r);
+        int off = (el * RS + v) * NPE + first;
+        asm volatile("" : "+v"(off));  // one address, constant offsets per node
+        double *line = svol + off;
+        double x[NP];
 #pragma unroll
-      for (int l = 0; l < NP; ++l) Drow[l] = sD[idx * NP + l];
+        for (int l = 0; l < NP; ++l) x[l] = line[l * stride];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        double s = 0.0;
+        for (int o = 0; o < NP; ++o) {
+          double s = 0.0;
 #pragma unroll
-        for (int l = 0; l < NP; ++l) s += Drow[l] * pen[v * NPE + l * stride];
-        acc[v] -= scale * s;
+          for (int l = 0; l < NP; ++l) s += Dm[o * NP + l] * x[l];
+          line[o * stride] = s;
+        }
       }
+      __syncthreads();
+      if (active) {
+        const double scale = sel3(d, A.scale[0], A.scale[1], A.scale[2]);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[v] -= scale * mybuf[v * NPE + a];
+      }
+    } else {
+      if (active) {
+        const int idx = sel3i(d, ci, cj, ck);
+        const int stride = sel3i(d, 1, NP, NF);
+        int base = a - idx * stride;
+        // keep the pencil's first node opaque, so that every read below is
+        // one address plus a constant offset (the compiler would otherwise
+        // re-derive each node's address from idx)
+        asm volatile("" : "+v"(base));
+        const double *pen = mybuf + base;
+        const double scale = sel3(d, A.scale[0], A.scale[1], A.scale[2]);
+        double Drow[NP];
+#pragma unroll
+        for (int l = 0; l < NP; ++l) Drow[l] = sD[idx * NP + l];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          double s = 0.0;
+#pragma unroll
+          for (int l = 0; l < NP; ++l) s += Drow[l] * pen[v * NPE + l * stride];
+          acc[v] -= scale * s;
+        }
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
 
   // (the limited stage, MOM, keeps every thread for the moment reduction)
@@ -709,15 +750,17 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
 // 1.32 ms with two rows between the stages instead of five (p and z; 28 rows
 // a stage on average instead of 34) and two elements per workgroup.
 // The operator on 32^3 elements of degree 4 (SR): 552 vector instructions per
-// wave and 68 VGPRs (7 waves per SIMD), 111 us at 4.1 TB/s of counted traffic,
-// of the 4.6 TB/s a large copy reaches here; with the neighbours found per
+// wave and 68 VGPRs (7 waves per SIMD), 111 us (and 99.5 with the volume term's
+// lines, below: 4.5 TB/s of counted traffic, of the 4.6 TB/s a large copy
+// reaches here); with the neighbours found per
 // lane and the wave speeds from three square roots and three reciprocals per
 // state, 704 instructions, 80 VGPRs and four spilled registers, 122 us.
-// (SR hydro is held to six waves per SIMD: its limited stage would take more
-// than 80 VGPRs, which was slower.)
+// (SR hydro is held to six waves per SIMD, which all its bodies meet without
+// spilling; SRMHD at degree 1 to five, where the compiler's choice of 98 VGPRs
+// allows four and ran the operator 4% slower.)
 template <int SYS, int N, int STAGE, int EPB_ = default_epb<SYS, N>(), bool MIXED = false, int FLUX = kLLF,
           bool MOM = false, bool PZ = false>
-__global__ void __launch_bounds__((RhsCfg<SYS, N, EPB_>::THREADS)) __attribute__((amdgpu_waves_per_eu(SYS == kSR ? 6 : 1)))
+__global__ void __launch_bounds__((RhsCfg<SYS, N, EPB_>::THREADS)) __attribute__((amdgpu_waves_per_eu(SYS == kSR ? 6 : (SYS == kMHD && N == 1 ? 5 : 1))))
 rhs_kernel(const RhsArgs A) {
   using C = RhsCfg<SYS, N, EPB_, FLUX, PZ>;
   __shared__ double smem[C::LDS + (MOM ? C::EPB : 0)];
