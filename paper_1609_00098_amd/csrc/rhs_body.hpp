@@ -164,6 +164,18 @@ typedef __attribute__((address_space(4))) const int64_t scalar_i64;
 typedef __attribute__((address_space(4))) const int32_t scalar_i32;
 typedef __attribute__((address_space(4))) const double scalar_f64;
 
+// Whether two elements' rows share LDS when a buffer of ROWS rows per element
+// is rewritten with NV rows per element (row r of element e at e * rows + r).
+template <int EPB, int NV, int ROWS>
+constexpr bool rows_overlap() {
+  for (int e = 0; e < EPB; ++e)
+    for (int v = 0; v < NV; ++v)
+      for (int e2 = 0; e2 < EPB; ++e2)
+        for (int v2 = 0; v2 < NV; ++v2)
+          if (e != e2 && e * ROWS + v == e2 * NV + v2) return true;
+  return false;
+}
+
 // The work of one workgroup on element group grp, with BT threads and the
 // LDS block smem (the kernels below choose grp and provide both).
 template <int SYS, int N, int STAGE, int EPB_, bool MIXED, int BT, int FLUX = kLLF, bool MOM = false, bool PZ = false>
@@ -691,6 +703,11 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
     // limited stage: recover every node of U^(s), then reduce each element to
     // the limiter's moments (the slope limiter runs next, over the grid)
     double *su = svol, *tabs = sD;
+    // su has NV rows per element where the volume buffer has RS.  By line, the
+    // last reads of the buffer (each node's derivatives) have no barrier behind
+    // them: where a row of one element becomes a row of another, every wave
+    // must have done them before any writes U^(s).
+    if constexpr (BY_LINE && rows_overlap<EPB, NV, RS>()) __syncthreads();
     if (active) {
       combine();
 #pragma unroll
