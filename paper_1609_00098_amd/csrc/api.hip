@@ -206,7 +206,7 @@ struct dgmi_ctx {
   double *d_bface = nullptr;      // exterior states per boundary face node, bface_copies times
   int bface_copies = 0;           // 3 with an analytic direction (one per RK stage), else 1
   int64_t boff[7] = {0};
-  double hbc[6 * 16] = {0};       // per box face: conserved [0, nv), primitives [9, 14), SRMHD z at 14
+  double hbc[6 * 16] = {0};       // per box face: conserved [0, nv), primitives [9, 14)
   double *d_bc = nullptr;         // device copy
   // slope limiter (uniform meshes)
   int lim_kind = 0;               // DGMI_LIMITER_*
@@ -1068,7 +1068,7 @@ static dgmi_status step_impl(dgmi_ctx *ctx, double *U, double *prim_inout, doubl
   // stage 1: U1 = U + dt L(U)
   a.U = U; a.P = prim_inout; a.a = 0.0; a.b = 1.0;
   if ((st = stage(0, b.U1, b.P1)) != DGMI_OK) return st;
-  a.in_pz = ctx->sys == 2 && !limit;
+  a.in_pe = ctx->sys == 2 && !limit;
   // stage 2: U2 = 3/4 U + 1/4 (U1 + dt L(U1))
   a.U = b.U1; a.P = b.P1; a.a = 0.75; a.b = 0.25;
   if ((st = stage(1, b.U2, b.P2)) != DGMI_OK) return st;
@@ -1171,7 +1171,6 @@ dgmi_status dgmi_set_boundary(dgmi_ctx *ctx, int32_t direction, const double *st
         default: dgmi::prim_to_cons<dgmi::kMHD>(P, st + 5, ctx->gamma, row); break;
       }
       row[9] = P.rho; row[10] = P.v[0]; row[11] = P.v[1]; row[12] = P.v[2]; row[13] = P.p;
-      if (ctx->sys == 2) row[14] = (P.rho + ctx->gamma / (ctx->gamma - 1.0) * P.p) / (1.0 - v2);  // z = rho h W^2
     }
     bc = 1;
   }

@@ -55,8 +55,8 @@ struct RhsArgs {
   int streamed;        // stage kernel: U^n is read and the output written past the caches (set where a stage's
                        // arrays exceed the last-level cache)
   int full_prims;      // stage kernel: write all five primitive rows (else NE/SR only p, SRMHD on uniform
-                       // meshes p and, in row 0, z = rho h W^2)
-  int in_pz;           // uniform SRMHD stage: the input's primitives are such a (p, z) pair
+                       // meshes p and, in row 0, the magnetic cubic's root em)
+  int in_pe;           // uniform SRMHD stage: the input's primitives are such a (p, em) pair
   const double *dtp;   // stage kernel: if set, dt is read from this device scalar
   // mixed degrees: the launch of degree N processes the nlist elements in
   // elist; per slot of elist, mtab holds [7] int64: the element's first
@@ -72,7 +72,7 @@ struct RhsArgs {
   // uniform meshes: a face whose neighbour index en is negative lies on box
   // face f; its nodes' exterior states (fixed or analytic) are the 16-double
   // rows bface[(boff[f] + (-1 - en) * (N+1)^2 + face node) * 16 + ...]:
-  // conserved [0, nv), primitives [9, 14), for SRMHD z = rho h W^2 at 14
+  // conserved [0, nv), primitives [9, 14)
   const double *bface;
   int64_t boff[7];
   // limited stage kernel: element moments [nelem][10][nv] and unphysical flags

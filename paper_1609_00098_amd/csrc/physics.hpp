@@ -518,36 +518,30 @@ DG_HD Prim sr_wave_state(const double *u, double p, double g, WaveState &w) {
   return P;
 }
 
-// SRMHD: velocity and wave quantities of a state whose pressure and
-// z = rho h W^2 are known, without the density: with T = S.B,
-// v = (S + (T / z) B) / (z + B^2) (the recovery's own closing formula),
-// B.v = T / z and rho h = z (1 - v^2).
-DG_HD Prim mhd_wave_state(const double *u, double p, double z, double g, WaveState &w) {
+// SRMHD: primitives of a state whose pressure p and root em = rho h W^2 + B^2 of
+// the magnetic cubic are known: with z = em - B^2 and T = S.B (B.v = T / z),
+// v = (S + (T / z) B) / em and rho = D sqrt(1 - v^2).  The recovery's closing
+// formula, and what it returns for its final (p, em), so that a kernel that
+// stores those two rebuilds the five primitives it returned.  An infinite em
+// marks the state at rest (D, 0, p) that a recovery without a bracket returns.
+DG_HD Prim mhd_prims(const double *u, double em, double p) {
   Prim P;
   const double BB = u[5] * u[5] + u[6] * u[6] + u[7] * u[7];
   const double T = u[1] * u[5] + u[2] * u[6] + u[3] * u[7];
-  const double em = z + BB;
-  const double r = fast_rcp(z * em);
-  const bool rest = z < 0.0;  // a failed recovery's state at rest, z = -rho h
-  const double Bv = rest ? 0.0 : T * (em * r), iem = rest ? 0.0 : z * r;
-  P.v[0] = (u[1] + Bv * u[5]) * iem;
-  P.v[1] = (u[2] + Bv * u[6]) * iem;
-  P.v[2] = (u[3] + Bv * u[7]) * iem;
+  const double z = em - BB;
+  const bool rest = em == __builtin_inf();
+  const double Tz = rest ? 0.0 : T * fast_rcp(z), iem = rest ? 0.0 : fast_rcp(em);
+  P.v[0] = (u[1] + Tz * u[5]) * iem;
+  P.v[1] = (u[2] + Tz * u[6]) * iem;
+  P.v[2] = (u[3] + Tz * u[7]) * iem;
+  P.rho = u[0] * fast_sqrt(1.0 - (sq(P.v[0]) + sq(P.v[1]) + sq(P.v[2])));
   P.p = p;
-  P.rho = 0.0;  // not formed
-  w.v2 = P.v[0] * P.v[0] + P.v[1] * P.v[1] + P.v[2] * P.v[2];
-  w.uu = 1.0 - w.v2;
-  const double rhoh = rest ? -z : z * w.uu, b2 = BB * w.uu + Bv * Bv;
-  w.A = g * p;
-  w.R_A = rhoh - w.A;
-  w.A += b2;
-  w.R = rhoh + b2;
   return P;
 }
 
 struct C2PResult {
   Prim P;
-  double z;  // MHD: rho h W^2 at the final pressure, or -rho h of the state at rest returned on failure
+  double em;  // MHD: with P.p, what mhd_prims takes to rebuild P (infinite where P is the state at rest)
   int iters;
   int ok;
 };
@@ -774,7 +768,7 @@ DG_HD C2PResult recover_as(const double *u, double g, double p0, double tol, int
   R.P.v[0] = R.P.v[1] = R.P.v[2] = 0.0;
   R.P.p = top;
   if (!(D > 0.0) || !(top > 0.0) || !(E > 0.0)) {
-    if (SYS == kMHD) R.z = -(D + g / gm1 * top);
+    if (SYS == kMHD) R.em = __builtin_inf();
     return R;
   }
   if (SYS == kSR && !(E * E - S2 > D * D)) return R;  // f(0) <= 0: no physical state
@@ -935,22 +929,19 @@ DG_HD C2PResult recover_as(const double *u, double g, double p0, double tol, int
   const double em = !TOL ? mhd_root_polished(e, dcub, em_prev, e_prev)
                          : (conv ? em_prev : mhd_root_near(e, dcub, em_prev, e_prev));
   const double z = em - BB;
-  R.z = z;
-  double Tz, iem;
+  R.em = em;
   if (TOL) {
     const double r = fast_rcp(z * em);
-    Tz = T * (em * r);
-    iem = z * r;
+    const double Tz = T * (em * r), iem = z * r;
+    R.P.v[0] = (S0 + Tz * u[5]) * iem;
+    R.P.v[1] = (S1 + Tz * u[6]) * iem;
+    R.P.v[2] = (S2c + Tz * u[7]) * iem;
+    R.P.p = p;
+    R.P.rho = D * fast_sqrt(1.0 - (sq(R.P.v[0]) + sq(R.P.v[1]) + sq(R.P.v[2])));
   } else {
-    Tz = T * fast_rcp(z);
-    iem = fast_rcp(em);
+    R.P = mhd_prims(u, em, p);
   }
-  R.P.v[0] = (S0 + Tz * u[5]) * iem;
-  R.P.v[1] = (S1 + Tz * u[6]) * iem;
-  R.P.v[2] = (S2c + Tz * u[7]) * iem;
   const double v2 = sq(R.P.v[0]) + sq(R.P.v[1]) + sq(R.P.v[2]);
-  R.P.p = p;
-  R.P.rho = D * fast_sqrt(1.0 - v2);
   R.ok = conv && (em > 0.0) && (z > 0.0) && (v2 < 1.0) && (p > 0.0) && (R.P.rho > 0.0);
   return R;
 }

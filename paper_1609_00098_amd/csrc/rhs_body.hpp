@@ -106,10 +106,10 @@ constexpr int default_epb() {
   return (N == 1) ? 8 : (N == 2) ? 9 : (N == 3) ? (SYS == kMHD ? 2 : 4) : (N == 4) ? (SYS == kMHD ? 2 : 1) : 1;
 }
 
-// PZ (SRMHD stages of dg_step after the first, see launch_one): the input's
-// primitive rows are 4, the pressure, and 0, z = rho h W^2, from which and U
-// the rest follows in closed form, instead of all five.
-template <int SYS, int N, int EPB_ = default_epb<SYS, N>(), int FLUX = kLLF, bool PZ = false>
+// PE (SRMHD stages of dg_step after the first, see launch_one): the input's
+// primitive rows are 4, the pressure, and 0, the cubic's root em, from which
+// and U mhd_prims rebuilds the five that the recovery returned.
+template <int SYS, int N, int EPB_ = default_epb<SYS, N>(), int FLUX = kLLF, bool PE = false>
 struct RhsCfg {
   static constexpr int NP = N + 1;
   static constexpr int NPE = NP * NP * NP;
@@ -128,8 +128,8 @@ struct RhsCfg {
   static constexpr int WORK = (SYS == kMHD && 3 * TPDP > EPB * NPE) ? 3 * TPDP : EPB * NPE;
   static constexpr int THREADS = ((WORK + 63) / 64) * 64;
   // primitive rows a node's state carries into the face phase: NE none (they
-  // follow from U), SR the pressure, SRMHD all five or (PZ) pressure and z
-  static constexpr int NPR = SYS == kSR ? 1 : (SYS == kMHD ? (PZ ? 2 : 5) : 0);
+  // follow from U), SR the pressure, SRMHD all five or (PE) pressure and em
+  static constexpr int NPR = SYS == kSR ? 1 : (SYS == kMHD ? (PE ? 2 : 5) : 0);
   static constexpr int RS = NV + NPR;  // rows per element in the volume buffer
   // LDS (doubles): the volume buffer [EPB][RS][NPE] (one direction's nodal
   // fluxes, then each node's state for the face phase), face slots
@@ -178,10 +178,10 @@ constexpr bool rows_overlap() {
 
 // The work of one workgroup on element group grp, with BT threads and the
 // LDS block smem (the kernels below choose grp and provide both).
-template <int SYS, int N, int STAGE, int EPB_, bool MIXED, int BT, int FLUX = kLLF, bool MOM = false, bool PZ = false>
+template <int SYS, int N, int STAGE, int EPB_, bool MIXED, int BT, int FLUX = kLLF, bool MOM = false, bool PE = false>
 __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem) {
-  using C = RhsCfg<SYS, N, EPB_, FLUX, PZ>;
-  static_assert(!PZ || (SYS == kMHD && STAGE == 1 && !MIXED && !MOM), "PZ: uniform SRMHD stages");
+  using C = RhsCfg<SYS, N, EPB_, FLUX, PE>;
+  static_assert(!PE || (SYS == kMHD && STAGE == 1 && !MIXED && !MOM), "PE: uniform SRMHD stages");
   static_assert(BT >= (N + 1) * (N + 1), "one thread per entry of D");
   constexpr int NP = C::NP, NPE = C::NPE, NF = C::NF, NV = C::NV, EPB = C::EPB, RS = C::RS;
   double *svol = smem;
@@ -340,7 +340,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
   };
   // raw values of a node, U and the primitive rows it carries: mesh node
   // `src` (kind 1) or row `src` of the boundary buffer (kind 2)
-  auto prow = [](int k) { return SYS == kSR ? 4 : (PZ ? 4 - 4 * k : k); };  // the k-th carried row
+  auto prow = [](int k) { return SYS == kSR ? 4 : (PE ? 4 - 4 * k : k); };  // the k-th carried row
   auto load_raw = [&](int kind, int64_t src, double *ue, double *pr) {
     if (MIXED || A.periodic) {
 #pragma unroll
@@ -353,22 +353,21 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
       const int64_t st = bnd ? 1 : nn;
 #pragma unroll
       for (int v = 0; v < NV; ++v) ue[v] = pu[v * st];
-      // (z of a box-face state is slot 14, after its primitives)
 #pragma unroll
-      for (int k = 0; k < C::NPR; ++k) pr[k] = pp[(PZ && bnd ? 4 + k : prow(k)) * st];
+      for (int k = 0; k < C::NPR; ++k) pr[k] = pp[prow(k) * st];
     }
   };
   constexpr int NPRX = C::NPR > 0 ? C::NPR : 1;
-  // primitives (of SR and PZ: velocity and pressure) and wave quantities of a
-  // state from U and the rows it carries
+  // primitives (of SR: velocity and pressure) and wave quantities of a state
+  // from U and the rows it carries
   auto state_waves = [&](const double *u, const double *pr, Prim &P, WaveState &w) {
     if constexpr (SYS == kSR) {
       P = sr_wave_state(u, pr[0], A.gamma, w);
-    } else if constexpr (PZ) {
-      P = mhd_wave_state(u, pr[0], pr[1], A.gamma, w);
     } else {
       if constexpr (SYS == kNE) {
         P = prims_at_pressure<kNE>(u, A.gamma, 0.0, A.poly);
+      } else if constexpr (PE) {
+        P = mhd_prims(u, pr[1], pr[0]);
       } else {
         P.rho = pr[0]; P.v[0] = pr[1]; P.v[1] = pr[2]; P.v[2] = pr[3]; P.p = pr[4];
       }
@@ -427,6 +426,13 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
         load_raw(kind, src, ue, pr);
       }
       state_waves(ue, pr, Pe, we);
+      if constexpr (PE) {
+        if (kind == 2) {  // a box-face state: its five primitives stand in its row
+          const double *row = A.bface + src + 9;
+          Pe = Prim{row[0], {row[1], row[2], row[3]}, row[4]};
+          we = wave_state<SYS>(ue, Pe, A.gamma, A.gratio);
+        }
+      }
     }
     flux_normal<SYS>(d, ue, Pe, Fe);
     if constexpr ((FLUX == kMarquina || FLUX == kRoe) && SYS == kNE) {
@@ -737,7 +743,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
   combine();
   const C2PResult R = recover<SYS>(us, A.gamma, P.p, 0.0, 100, A.poly);
   // intermediate stages keep only what the next one reads: the pressure and,
-  // on uniform SRMHD meshes, z in row 0 (mixed ones keep all five rows); the
+  // on uniform SRMHD meshes, em in row 0 (mixed ones keep all five rows); the
   // caller's buffers get all five
   if (A.full_prims || (SYS == kMHD && MIXED)) {  // rows the next stage does not read: streamed
     if (SYS == kMHD && MIXED && !A.full_prims) {
@@ -753,7 +759,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
       __builtin_nontemporal_store(R.P.v[2], &A.Pout[3 * nn + q]);
     }
   } else if (SYS == kMHD) {
-    A.Pout[q] = R.z;
+    A.Pout[q] = R.em;
   }
   A.Pout[4 * nn + q] = R.P.p;
   if (!R.ok) atomicAdd(A.nfail, 1ull);
@@ -764,8 +770,11 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
 // The RK stages of 64^3 SRMHD elements of degree 3 (16.8M nodes): 1.73 -> 1.50
 // ms a stage on average since the first stage does not read U^n (weight 0; its
 // lines had left L2 by then) and large meshes stream U^n and the output, ->
-// 1.32 ms with two rows between the stages instead of five (p and z; 28 rows
-// a stage on average instead of 34) and two elements per workgroup.
+// 1.32 ms with two rows between the stages instead of five (28 rows a stage on
+// average instead of 34) and two elements per workgroup.  (The second row was
+// z = rho h W^2 then, rho h formed as z (1 - v^2): a relative error of W^2 ulps
+// where the five rows have none in the pressure's part.  With em and the
+// recovery's own formulas, a square root and a reciprocal more per state, 1.36.)
 // The operator on 32^3 elements of degree 4 (SR): 552 vector instructions per
 // wave and 68 VGPRs (7 waves per SIMD), 111 us (and 99.5 with the volume term's
 // lines, below: 4.5 TB/s of counted traffic, of the 4.6 TB/s a large copy
@@ -776,10 +785,10 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
 // spilling; SRMHD at degree 1 to five, where the compiler's choice of 98 VGPRs
 // allows four and ran the operator 4% slower.)
 template <int SYS, int N, int STAGE, int EPB_ = default_epb<SYS, N>(), bool MIXED = false, int FLUX = kLLF,
-          bool MOM = false, bool PZ = false>
+          bool MOM = false, bool PE = false>
 __global__ void __launch_bounds__((RhsCfg<SYS, N, EPB_>::THREADS)) __attribute__((amdgpu_waves_per_eu(SYS == kSR ? 6 : (SYS == kMHD && N == 1 ? 5 : 1))))
 rhs_kernel(const RhsArgs A) {
-  using C = RhsCfg<SYS, N, EPB_, FLUX, PZ>;
+  using C = RhsCfg<SYS, N, EPB_, FLUX, PE>;
   __shared__ double smem[C::LDS + (MOM ? C::EPB : 0)];
   // XCD-major block order: hardware block b runs on XCD b % 8, which walks
   // its own contiguous range of the processing order.
@@ -788,7 +797,7 @@ rhs_kernel(const RhsArgs A) {
   if (seq >= A.nblocks) return;
   int grp = seq;
   if constexpr (!MIXED) grp = A.bm.S ? brick_map(seq, A.bm) : seq;
-  rhs_body<SYS, N, STAGE, EPB_, MIXED, C::THREADS, FLUX, MOM, PZ>(A, grp, smem);
+  rhs_body<SYS, N, STAGE, EPB_, MIXED, C::THREADS, FLUX, MOM, PE>(A, grp, smem);
 }
 
 // The RK stage that also writes the limiter's moments.
@@ -817,7 +826,7 @@ hipError_t launch_one(int stage, const RhsArgs &a, hipStream_t s) {
   const int grid = ((b.nblocks + 7) / 8) * 8;
   if (stage == 0)
     hipLaunchKernelGGL((rhs_kernel<SYS, N, 0, C::EPB, false, FLUX>), dim3(grid), dim3(C::THREADS), 0, s, b);
-  else if (SYS == kMHD && a.in_pz)
+  else if (SYS == kMHD && a.in_pe)
     hipLaunchKernelGGL((rhs_kernel<SYS, N, 1, C::EPB, false, FLUX, false, SYS == kMHD>), dim3(grid), dim3(C::THREADS), 0,
                        s, b);
   else
