@@ -730,15 +730,13 @@ DG_HD bool mhd_f0(const double *u, double g, double *f, double *em_out, double *
 // which start the first evaluation's (em0 <= 0: none).  TOL: tolerance mode
 // (tol > 0), else polish mode.
 //
-// The iteration runs first without the record of the smallest |f| (a last
-// resort that a converged point never needs), for up to kPlainIters
-// evaluations; a point that has not converged by then starts over with it and
-// all maxit, so that its result is that of one tracked run.  For SRMHD in
-// tolerance mode, with the cubic's start and stop above, shared reciprocals and
-// the modes compiled apart, 1,284 -> 886 vector instructions a point (f(0) seed),
-// 1,002 -> 755 us for 2.5e7 points: vector issue bound it at 83%, 77% now.
-constexpr int kPlainIters = 16;
-
+// Bound by vector issue.  With the cubic's start and stop above and the modes
+// compiled apart, SRMHD to 1e-10 from the f(0) seed takes 781 us for 2.5e7 points
+// (980 before).  Polish mode keeps no more of the smallest |f| than the value and
+// its pressure, and tests it afterwards.  (A first loop without that record, and
+// the points beyond 16 evaluations started over with it, was as fast where all
+// settle sooner, but took 44 us for 10^5 SRMHD points from the plain seed and
+// 84 us for 4x10^5 SR points at Lorentz factors of 1,000: 31.5 and 53 now.)
 template <int SYS, bool TOL>
 DG_HD C2PResult recover_as(const double *u, double g, double p0, double tol, int maxit, bool poly, double em0,
                            double e0) {
@@ -775,22 +773,16 @@ DG_HD C2PResult recover_as(const double *u, double g, double p0, double tol, int
   const double Sabs = SYS == kSR ? fast_sqrt(S2) : 0.0;
   const double pstart = (p0 > 0.0 && p0 < top) ? p0 : top;
   double p = pstart, em_prev = em0, e_prev = e0;
-  // the evaluated pressure with the smallest |f|, and whether that |f| lies
-  // within the rounding of f's terms (a last resort when the iteration runs
-  // out: for an extreme Lorentz factor 1 - v^2 cancels and f carries noise
-  // far above 1e-14 p, so neither the step tests nor the bracket settle)
-  double p_best = p;
-  bool best_at_floor = false;
-  auto iterate = [&](auto track_, int cap) __attribute__((always_inline)) {
-    constexpr bool track = decltype(track_)::value;
-    double lo = 0.0, hi = top;
-    double f_best = 1e300, prev_step = 1e300;
+  // polish mode: the evaluated pressure with the smallest |f|, the result where
+  // the iteration runs out with that |f| within the rounding of f's terms (for
+  // an extreme Lorentz factor 1 - v^2 cancels and f carries noise far above
+  // 1e-14 p, so neither the step tests nor the bracket settle)
+  double p_best = p, f_best = 1e300;
+  auto iterate = [&]() __attribute__((always_inline)) {
+    double lo = 0.0, hi = top, prev_step = 1e300;
     bool last_small = false;
-    p = p_best = pstart;
-    em_prev = em0;
-    e_prev = e0;
 #pragma unroll 1
-    for (int it = 1; it <= cap; ++it) {
+    for (int it = 1; it <= maxit; ++it) {
       R.iters = it;
       int valid = 1;
       double v2, e = 0.0, z, em = 0.0, W;
@@ -844,11 +836,9 @@ DG_HD C2PResult recover_as(const double *u, double g, double p0, double tol, int
       }
       const double rho_eps = z * uu - D * sqw - p;
       const double f = gm1 * rho_eps - p;
-      if (track && fabs(f) < f_best) {
+      if (!TOL && fabs(f) < f_best) {
         f_best = fabs(f);
         p_best = p;
-        // |f| <= 32 eps (g-1) (z + D / sqrt(1 - v^2)), without the division
-        best_at_floor = f_best * sqw <= 7.105427357601002e-15 * gm1 * (z * sqw + D);
       }
       // |f| W^2 / ((g-1) E) is the backward residual |tau(P) - tau| / E of the
       // primitives at p to first order (and bounds the momentum's); 1% of
@@ -901,10 +891,19 @@ DG_HD C2PResult recover_as(const double *u, double g, double p0, double tol, int
     }
     return 0;
   };
-  int conv = iterate(std::false_type{}, maxit < kPlainIters ? maxit : kPlainIters);
-  if (!conv) {
-    conv = iterate(std::true_type{}, maxit);
-    if (!conv && !TOL && best_at_floor) {
+  int conv = iterate();
+  if (!TOL && !conv && f_best < 1e300) {
+    // |f| <= 32 eps (g-1) (z + D / sqrt(1 - v^2)), without the division
+    double z, sqw;
+    if (SYS == kSR) {
+      z = E + p_best;
+      sqw = fast_sqrt((z - Sabs) * (z + Sabs)) * fast_rcp(z);
+    } else {
+      const double em = mhd_root_polished(E + p_best + 0.5 * BB, dcub, -1.0, 0.0);
+      z = em - BB;
+      sqw = fast_sqrt(1.0 - (S2 * z * z + T * T * (z + em)) * fast_rcp(z * z * em * em));
+    }
+    if (f_best * sqw <= 7.105427357601002e-15 * gm1 * (z * sqw + D)) {
       p = p_best;
       conv = 1;
     }
