@@ -57,47 +57,6 @@ __host__ __device__ __forceinline__ void mlp_features(const double *u, double g,
   x[4] = (float)log(f0 / D);
 }
 
-// ln x of a positive double to FP32 accuracy (also below the FP32 range): the
-// hardware's log2 of the mantissa, plus the exponent.
-__device__ __forceinline__ float log_to_float(double x) {
-  const float m = (float)__builtin_amdgcn_frexp_mant(x);
-  return ((float)__builtin_amdgcn_frexp_exp(x) + __builtin_amdgcn_logf(m)) * 0.693147181f;
-}
-
-// ln(1 + s) for s >= 0, the rounding of 1 + s put back to first order.
-__device__ __forceinline__ float log1_fast(float s) {
-  const float t = 1.0f + s;
-  return fmaf(s - (t - 1.0f), __builtin_amdgcn_rcpf(t), __logf(t));
-}
-
-// The same features for the recovery's seed, from the hardware's FP32 logarithms,
-// roots and reciprocals (within an ulp or two of mlp_features' library calls,
-// which with its FP64 logarithm and divisions take about 500 instructions more
-// per point).
-template <int SYS>
-__device__ __forceinline__ void seed_features(const double *u, double g, float *x) {
-  const double D = u[0], tau = u[4];
-  const double S2 = u[1] * u[1] + u[2] * u[2] + u[3] * u[3];
-  double BB = 0.0, SB = 0.0, f0 = 0.0;
-  bool defined;
-  if (SYS == 2) {
-    BB = u[5] * u[5] + u[6] * u[6] + u[7] * u[7];
-    SB = u[1] * u[5] + u[2] * u[6] + u[3] * u[7];
-    double em, e;
-    defined = mhd_f0(u, g, &f0, &em, &e);
-  } else {
-    defined = pressure_function<SYS>(u, g, 0.0, &f0);
-  }
-  if (!defined || !(f0 > 0.0)) f0 = 1e-300 * D;
-  const float Df = (float)D, r = __builtin_amdgcn_rcpf(Df), iD = fmaf(fmaf(-Df, r, 1.0f), r, r);
-  const float Sa = __builtin_amdgcn_sqrtf((float)S2), Ba = __builtin_amdgcn_sqrtf((float)BB);
-  x[0] = __logf((float)tau * iD);
-  x[1] = log1_fast(Sa * iD);
-  x[2] = log1_fast((float)BB * iD);
-  x[3] = (float)SB * __builtin_amdgcn_rcpf(Sa * Ba + 1e-30f);
-  x[4] = log_to_float(f0 * fast_rcp(D));
-}
-
 // ---------------------------------------------------------------------
 // Inference on the matrix cores.  A wave evaluates 32 samples at a time with
 // both layers transposed, [units x inputs] x [inputs x samples] in 32 x 32
@@ -252,12 +211,15 @@ __device__ __forceinline__ float mlp_net32(const MlpNet *s, float x0, float x1, 
 }
 
 // Recovery seed D exp(y) of this lane's point, all 64 lanes of a wave together
-// (every lane must take part): its points as two passes of 32.
+// (every lane must take part): its points as two passes of 32.  The features are
+// the training's own (with hardware FP32 logarithms, roots and reciprocals in
+// their place 4x10^6 SRMHD points took 349 us instead of 410, but the seeds
+// were undefined where D has no FP32 reciprocal).
 template <int SYS>
 __device__ __forceinline__ double mlp_seed_wave(const MlpNet *s, const double *u, double g) {
   const bool lo = (threadIdx.x & 63) < 32;
   float x[kIn];
-  seed_features<SYS>(u, g, x);
+  mlp_features<SYS>(u, g, x);
 #pragma unroll
   for (int i = 0; i < kIn; ++i) {
     const float c = x[i] - s->mu[i];

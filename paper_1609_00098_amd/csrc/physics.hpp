@@ -698,10 +698,9 @@ DG_HD double mhd_root_polished(double e, double d, double em_prev, double e_prev
   return cubic_top_root(e, d, em_prev > 0.0 ? mhd_start(e, em_prev, e_prev) : e);
 }
 
-// f(0), the seed of recoveries to a tolerance (f(0) mode, the network's feature):
-// the pressure function at zero
-// pressure, with the cubic's root em and coefficient e there.  False where it is
-// undefined (as pressure_function).
+// f(0), the seed of SRMHD recoveries to a tolerance in f(0) mode: the pressure
+// function at zero pressure, with the cubic's root em and coefficient e there.
+// False where it is undefined (as pressure_function).
 DG_HD bool mhd_f0(const double *u, double g, double *f, double *em_out, double *e_out) {
   const double D = u[0], tau = u[4];
   const double S2 = u[1] * u[1] + u[2] * u[2] + u[3] * u[3];
