@@ -78,7 +78,8 @@ __host__ __device__ __forceinline__ void mlp_features(const double *u, double g,
 // In FP32 the products alone occupy a SIMD for 4,480 cycles per 32 samples and
 // do not run beside the vector unit's 2,800 cycles of activations (half of
 // them exp and reciprocal): 90 us for 10^6 samples.  Split, they take 1,920
-// cycles on cores the activations leave free: 62 us.
+// cycles on cores the activations leave free: 62 us (before the rounded quotients
+// of silu).
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -141,12 +142,24 @@ __device__ __forceinline__ void mlp_net_load(const float *p, MlpNet *s) {
   }
 }
 
-// x sigmoid(x), the reciprocal from the hardware estimate (within one ulp)
-__device__ __forceinline__ float silu_fast(float x) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
+// x sigmoid(x).  ROUNDED: the correctly rounded quotient x / (1 + e^-x), for
+// mlp_forward, whose outputs are results: the hardware's reciprocal, one
+// correction, the special cases put right; both sides by a quarter, so that the
+// reciprocal is a normal number to the end of the exponential's range.  Else the
+// reciprocal alone (within one ulp, 0 below -87), for the recovery's seed.
+template <bool ROUNDED>
+__device__ __forceinline__ float silu(float x) {
+  const float e = __expf(-x);
+  if (!ROUNDED) return x * __builtin_amdgcn_rcpf(1.0f + e);
+  const float n = 0.25f * x, d = fmaf(0.25f, e, 0.25f);
+  const float r = __builtin_amdgcn_rcpf(d), q = n * r;
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-q, d, n), r, q), d, n);
+}
 
 // Normalised output for 32 samples, all 64 lanes of the wave together: lane l
 // passes inputs l / 32, 2 + l / 32 and 4 + l / 32 (the sixth being 1) of sample
 // l % 32 and receives that sample's output.
+template <bool ROUNDED>
 __device__ __forceinline__ float mlp_net32(const MlpNet *s, float x0, float x1, float x2) {
   const int r = threadIdx.x & 31, h = (threadIdx.x >> 5) & 1;
   const float xb[3] = {x0, x1, x2};
@@ -184,7 +197,7 @@ __device__ __forceinline__ float mlp_net32(const MlpNet *s, float x0, float x1, 
 #pragma unroll
     for (int j = 0; j < 8; j += 2) {
       const int a = 8 * (k & 1) + j;
-      split3(float2_t{silu_fast(H[k >> 1][a]), silu_fast(H[k >> 1][a + 1])}, f, j);
+      split3(float2_t{silu<ROUNDED>(H[k >> 1][a]), silu<ROUNDED>(H[k >> 1][a + 1])}, f, j);
     }
     // the smallest products first
 #pragma unroll
@@ -204,7 +217,7 @@ __device__ __forceinline__ float mlp_net32(const MlpNet *s, float x0, float x1, 
     for (int q = 0; q < 4; ++q) {
       const float4_t w = *reinterpret_cast<const float4_t *>(&s->w3[32 * m + 8 * q + 4 * h]);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) y[m] += w[c] * silu_fast(E[m][4 * q + c]);
+      for (int c = 0; c < 4; ++c) y[m] += w[c] * silu<ROUNDED>(E[m][4 * q + c]);
     }
   const float yl = y[0] + y[1];
   return yl + __shfl_xor(yl, 32) + s->b3;
@@ -233,7 +246,7 @@ __device__ __forceinline__ double mlp_seed_wave(const MlpNet *s, const double *u
   for (int p = 0; p < 2; ++p) {  // (rolled: one pass's registers at a time)
     const bool own = lo == (p == 0);
     const float x0 = own ? (lo ? x[0] : x[1]) : o0, x1 = own ? (lo ? x[2] : x[3]) : o1;
-    const float yp = mlp_net32(s, x0, x1, lo ? (p == 0 ? x[4] : o2) : 1.0f);
+    const float yp = mlp_net32<false>(s, x0, x1, lo ? (p == 0 ? x[4] : o2) : 1.0f);
     if (own) y = yp;
   }
   y = y * s->ysd + s->ymu;
