@@ -208,6 +208,9 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
   }
   const int ci = a % NP, cj = (a / NP) % NP, ck = a / NF;
   const int64_t nn = A.nnodes;
+  // (the polytropic gas is for uniform meshes: left in, its power function takes
+  // the mixed NE kernel from 76 to 112 VGPRs and from six to four waves per SIMD)
+  const bool poly = !MIXED && A.poly;
   // A workgroup of a uniform mesh owns consecutive nodes: its rows start at
   // scalar addresses and a lane adds its thread index (elements of a mixed
   // list are anywhere).
@@ -365,7 +368,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
       P = sr_wave_state(u, pr[0], A.gamma, w);
     } else {
       if constexpr (SYS == kNE) {
-        P = prims_at_pressure<kNE>(u, A.gamma, 0.0, A.poly);
+        P = prims_at_pressure<kNE>(u, A.gamma, 0.0, poly);
       } else if constexpr (PE) {
         P = mhd_prims(u, pr[1], pr[0]);
       } else {
@@ -442,7 +445,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
         ui[v] = own[v * NPE];
         fi[v] = slot[v * 6 * NF];
       }
-      const Prim Pi = prims_at_pressure<kNE>(ui, A.gamma, 0.0, A.poly);
+      const Prim Pi = prims_at_pressure<kNE>(ui, A.gamma, 0.0, poly);
       const double sg = side ? 1.0 : -1.0;
       if constexpr (FLUX == kMarquina) {
         double Fs[5];
@@ -718,7 +721,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
       combine();
 #pragma unroll
       for (int v = 0; v < NV; ++v) su[(le * NV + v) * NPE + a] = us[v];
-      const C2PResult R = recover<SYS>(us, A.gamma, P.p, 0.0, 100, A.poly);
+      const C2PResult R = recover<SYS>(us, A.gamma, P.p, 0.0, 100, poly);
       if (SYS == kMHD || A.full_prims) {
         A.Pout[q] = R.P.rho;
         A.Pout[nn + q] = R.P.v[0];
@@ -741,7 +744,7 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
     return;
   }
   combine();
-  const C2PResult R = recover<SYS>(us, A.gamma, P.p, 0.0, 100, A.poly);
+  const C2PResult R = recover<SYS>(us, A.gamma, P.p, 0.0, 100, poly);
   // intermediate stages keep only what the next one reads: the pressure and,
   // on uniform SRMHD meshes, em in row 0 (mixed ones keep all five rows); the
   // caller's buffers get all five
@@ -782,11 +785,12 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
 // lane and the wave speeds from three square roots and three reciprocals per
 // state, 704 instructions, 80 VGPRs and four spilled registers, 122 us.
 // (SR hydro is held to six waves per SIMD, which all its bodies meet without
-// spilling; SRMHD at degree 1 to five, where the compiler's choice of 98 VGPRs
-// allows four and ran the operator 4% slower.)
+// spilling; SRMHD at degrees 1 and 5 to five, where the compiler's choice of 98
+// to 100 VGPRs allows four: the operator took 4% longer at degree 1 and 683 us
+// instead of 602 on 33^3 elements of degree 5.)
 template <int SYS, int N, int STAGE, int EPB_ = default_epb<SYS, N>(), bool MIXED = false, int FLUX = kLLF,
           bool MOM = false, bool PE = false>
-__global__ void __launch_bounds__((RhsCfg<SYS, N, EPB_>::THREADS)) __attribute__((amdgpu_waves_per_eu(SYS == kSR ? 6 : (SYS == kMHD && N == 1 ? 5 : 1))))
+__global__ void __launch_bounds__((RhsCfg<SYS, N, EPB_>::THREADS)) __attribute__((amdgpu_waves_per_eu(SYS == kSR ? 6 : (SYS == kMHD && ((N == 1 && !MIXED) || N == 5) ? 5 : 1))))
 rhs_kernel(const RhsArgs A) {
   using C = RhsCfg<SYS, N, EPB_, FLUX, PE>;
   __shared__ double smem[C::LDS + (MOM ? C::EPB : 0)];
