@@ -117,14 +117,43 @@ __device__ __forceinline__ void map_lines(double *buf, scalar_f64 *M) {
   __syncthreads();
 }
 
+// The same map with a lane per output node, o and r from its index as the output
+// lies in buf; the matrix from LDS.  Results stay in the lane's registers.
+template <int NCH, int NI, int NO, int NR, bool FIRST>
+__device__ __forceinline__ void map_nodes(const double *buf, const double *sM, double (&out)[NCH]) {
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) out[c] = 0.0;
+  const int l = threadIdx.x;
+  if (l < NO * NR) {
+    const int o = FIRST ? l % NO : l / NR, r = FIRST ? l / NO : l % NR;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const double w = sM[o * 8 + i];
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) out[c] += w * buf[c * kChan + (FIRST ? i + NI * r : r + NR * i)];
+    }
+  }
+}
+
+// A lane's channels to its place in buf, every lane's reads done before.
+template <int NCH>
+__device__ __forceinline__ void put_channels(double *buf, const double (&v)[NCH], int n) {
+  __syncthreads();
+  if ((int)threadIdx.x < n) {
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) buf[c * kChan + threadIdx.x] = v[c];
+  }
+  __syncthreads();
+}
+
 }  // namespace
 
 
 // The work of one face (wave) between degrees NLO < NMX, every loop bound a
 // compile-time constant.
-template <int SYS, int FLUX, int NLO, int NMX>
+template <int SYS, int FLUX, bool LINES, int NLO, int NMX>
 __device__ __forceinline__ void mortar_face(const MortarArgs &A, int64_t qhi, int64_t qlo, int64_t ohi, int64_t olo,
-                                            int d, int side_hi, double *buf) {
+                                            int d, int side_hi, double *buf, double *sI, double *sP) {
   constexpr int NV = SysTraits<SYS>::nv, NS = Interp<SYS>::ns;
   // channels interpolated to the mortar: the state, then the lower side's
   // nodal normal fluxes
@@ -137,6 +166,10 @@ __device__ __forceinline__ void mortar_face(const MortarArgs &A, int64_t qhi, in
   const int64_t nn = A.nnodes;
   constexpr int tab = (NLO * 8 + NMX) * 64;
   scalar_f64 *I = (scalar_f64 *)(A.Itab + tab), *Pm = (scalar_f64 *)(A.Ptab + tab);  // I[ma][ia], P[a][ma]
+  if constexpr (!LINES) {
+    sI[l] = A.Itab[tab + l];
+    sP[l] = A.Ptab[tab + l];
+  }
 
   // the higher side's node of this lane's mortar position, loaded up front so
   // that its latency overlaps the lower side's loads
@@ -180,15 +213,21 @@ __device__ __forceinline__ void mortar_face(const MortarArgs &A, int64_t qhi, in
   __syncthreads();
 
   // I1, I2: the channels at the mortar nodes, one tangential direction at a time
-  map_lines<NC, nl, nm, nl, true>(buf, I);
-  map_lines<NC, nl, nm, nm, false>(buf, I);
+  double s[NC];
+  if constexpr (LINES) {
+    map_lines<NC, nl, nm, nl, true>(buf, I);
+    map_lines<NC, nl, nm, nm, false>(buf, I);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) s[c] = buf[c * kChan + l];
+  } else {
+    map_nodes<NC, nl, nm, nl, true>(buf, sI, s);
+    put_channels<NC>(buf, s, nm * nl);
+    map_nodes<NC, nl, nm, nm, false>(buf, sI, s);
+  }
 
   // flux at the mortar node
   double jr[NV];
   if (l < nm * nm) {
-    double s[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) s[c] = buf[c * kChan + l];
     double ul[NV], Fl[NV];
     Prim Pl;
     interp_to_state<SYS>(s, A.gamma, ul, Pl);
@@ -231,20 +270,24 @@ __device__ __forceinline__ void mortar_face(const MortarArgs &A, int64_t qhi, in
       }
     }
   }
-  __syncthreads();
-  if (l < nm * nm) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) buf[v * kChan + l] = jr[v];
-  }
-  __syncthreads();
+  put_channels<NV>(buf, jr, nm * nm);
 
   // P1, P2: lower side's lift term P (F*.n_lo - I F_h.n_lo) at its nodes
-  map_lines<NV, nm, nl, nm, true>(buf, Pm);
-  map_lines<NV, nm, nl, nl, false>(buf, Pm);
+  double g[NV];
+  if constexpr (LINES) {
+    map_lines<NV, nm, nl, nm, true>(buf, Pm);
+    map_lines<NV, nm, nl, nl, false>(buf, Pm);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) g[v] = buf[v * kChan + l];
+  } else {
+    map_nodes<NV, nm, nl, nm, true>(buf, sP, g);
+    put_channels<NV>(buf, g, nl * nm);
+    map_nodes<NV, nm, nl, nl, false>(buf, sP, g);
+  }
   if (l < nl * nl) {
     double *out_lo = A.facebuf + olo + l;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) out_lo[v * nl * nl] = buf[v * kChan + l];
+    for (int v = 0; v < NV; ++v) out_lo[v * nl * nl] = g[v];
   }
 }
 
@@ -258,20 +301,21 @@ __device__ __forceinline__ void mortar_face(const MortarArgs &A, int64_t qhi, in
 //      F*.n_lo - I F_h.n_lo;
 //   P1, P2 project that difference onto the lower side's nodes along each
 //      direction.
-// The maps run a lane per line with the matrix on the scalar side (map_lines).
-// (A lane per output node read every input value once per output from LDS: 230
-// LDS reads a face, which alone took 15 of the 24.8 us of the pass over 16^3
-// elements of degrees 2 to 7 (10,200 faces), at 140 VGPRs; now about 80 reads
-// and 71 VGPRs: a mixed RK3 step of three passes went from 186 to 171 us.)
+// LINES: the maps run a lane per line with the matrix on the scalar side
+// (map_lines), about 80 LDS reads a face and 71 VGPRs.  Else a lane per output
+// node reads every input value once per output: 230 LDS reads and 140 VGPRs, which
+// bound a pass over many faces, but a shorter chain, which is what counts where
+// every face runs at once (few_faces below).
 // Workgroups are mapped XCD-major (hardware block b runs on XCD b % 8 and
 // walks its own contiguous range of the face list), so that faces of nearby
 // elements, which share cache lines of the node blocks, share an L2.  The
 // degree pair selects a body compiled for it (every face of a wave has the
 // same pair, so the branch is uniform).
-template <int SYS, int FLUX>
+template <int SYS, int FLUX, bool LINES>
 __global__ void __launch_bounds__(64) mortar_kernel(const MortarArgs A) {
   constexpr int NC = Interp<SYS>::ns + SysTraits<SYS>::nv;
   __shared__ double buf[NC * kChan];
+  __shared__ double sI[LINES ? 1 : 64], sP[LINES ? 1 : 64];
   const int64_t per = (A.nfaces + 7) >> 3;
   const int64_t t = (int64_t)(blockIdx.x & 7) * per + (int64_t)(blockIdx.x >> 3);
   if (t >= A.nfaces) return;
@@ -280,7 +324,7 @@ __global__ void __launch_bounds__(64) mortar_kernel(const MortarArgs A) {
   const int info = (int)fd[4];
   const int d = info & 3, side_hi = (info >> 2) & 1, Nm = (info >> 3) & 7, Nlo = (info >> 6) & 7;
 #define DGMI_MORTAR_CASE(LO, HI) \
-  case LO * 8 + HI: mortar_face<SYS, FLUX, LO, HI>(A, qhi, qlo, ohi, olo, d, side_hi, buf); break;
+  case LO * 8 + HI: mortar_face<SYS, FLUX, LINES, LO, HI>(A, qhi, qlo, ohi, olo, d, side_hi, buf, sI, sP); break;
   switch (Nlo * 8 + Nm) {
     DGMI_MORTAR_CASE(1, 2) DGMI_MORTAR_CASE(1, 3) DGMI_MORTAR_CASE(1, 4) DGMI_MORTAR_CASE(1, 5)
     DGMI_MORTAR_CASE(1, 6) DGMI_MORTAR_CASE(1, 7) DGMI_MORTAR_CASE(2, 3) DGMI_MORTAR_CASE(2, 4)
@@ -321,25 +365,34 @@ __global__ void __launch_bounds__(256) fill_kernel(double *p, int64_t n, double 
 }
 
 // ------------------------------------------------------------ launchers
+// Whether every face runs at once with a lane per node: twelve waves per CU for
+// NE and SR (140 VGPRs), eight for SRMHD (174).  Then the chain of one face counts,
+// which is shorter than by line, else the work.  Us a pass, by node / by line, of
+// degrees 2 to 7: NE 168 faces 4.6 / 6.3, 1,304 7.0 / 8.2, 3,336 13.2 / 13.3,
+// 10,272 23.3 / 20.4; SR 5.0 / 6.3, 7.6 / 9.2, 14.1 / 14.0, 25.4 / 23.5; SRMHD 5.7 /
+// 9.2, 11.8 / 13.4, 1,808 faces 13.4 / 15.0, 2,504 17.3 / 16.3, 10,272 42.2 / 38.7.
+static bool few_faces(int sys, int64_t n) { return n <= 256 * (sys == kMHD ? 8 : 12); }
+
+template <int SYS>
+static void mortar_sys(bool hll, const MortarArgs &a, hipStream_t s) {
+  const dim3 grid((unsigned)(((a.nfaces + 7) >> 3) << 3)), block(64);
+  if (few_faces(SYS, a.nfaces)) {
+    if (hll) hipLaunchKernelGGL((mortar_kernel<SYS, kHLL, false>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((mortar_kernel<SYS, kLLF, false>), grid, block, 0, s, a);
+  } else {
+    if (hll) hipLaunchKernelGGL((mortar_kernel<SYS, kHLL, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((mortar_kernel<SYS, kLLF, true>), grid, block, 0, s, a);
+  }
+}
+
 hipError_t launch_mortar(int sys, int flux, const MortarArgs &a, hipStream_t s) {
   if (a.nfaces <= 0) return hipSuccess;
   if (a.nfaces > ((int64_t)1 << 31) - 1) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(((a.nfaces + 7) >> 3) << 3)), block(64);
   if (flux != kLLF && flux != kHLL) return hipErrorInvalidValue;
-  const bool hll = flux == kHLL;
   switch (sys) {
-    case kNE:
-      if (hll) hipLaunchKernelGGL((mortar_kernel<kNE, kHLL>), grid, block, 0, s, a);
-      else hipLaunchKernelGGL((mortar_kernel<kNE, kLLF>), grid, block, 0, s, a);
-      break;
-    case kSR:
-      if (hll) hipLaunchKernelGGL((mortar_kernel<kSR, kHLL>), grid, block, 0, s, a);
-      else hipLaunchKernelGGL((mortar_kernel<kSR, kLLF>), grid, block, 0, s, a);
-      break;
-    case kMHD:
-      if (hll) hipLaunchKernelGGL((mortar_kernel<kMHD, kHLL>), grid, block, 0, s, a);
-      else hipLaunchKernelGGL((mortar_kernel<kMHD, kLLF>), grid, block, 0, s, a);
-      break;
+    case kNE: mortar_sys<kNE>(flux == kHLL, a, s); break;
+    case kSR: mortar_sys<kSR>(flux == kHLL, a, s); break;
+    case kMHD: mortar_sys<kMHD>(flux == kHLL, a, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
