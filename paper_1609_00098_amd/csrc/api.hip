@@ -424,10 +424,14 @@ static dgmi_status mixed_setup(dgmi_ctx *c, const std::vector<double> &hx, hipSt
 }
 
 // Whether an RK stage streams U^n and its output past the caches: its arrays
-// (U, U^n and the output, pressures in and out) exceed the 256 MiB last-level
-// cache, so that the next stage would not find them there anyway.
+// (U, U^n and the output, pressures in and out) exceed one and a half times the
+// 256 MiB last-level cache, so that the next stage would find little of them
+// there.  Below, a part that stays is worth more: us a step kept / streamed, NE
+// degree 4 285 MiB 191 / 228, 356 MiB 267 / 277, 531 MiB 417 / 411; SR degree 3
+// 298 MiB 277 / 286, 356 MiB 331 / 331, 531 MiB 504 / 488; SRMHD degree 3 311 MiB
+// 337 / 334, 422 MiB 460 / 451, 1,566 MiB 1,701 / 1,671.
 static int stage_streams(const dgmi_ctx *c) {
-  return 8 * (int64_t)(3 * c->nv + 2) * c->nnodes > ((int64_t)256 << 20);
+  return 8 * (int64_t)(3 * c->nv + 2) * c->nnodes > ((int64_t)384 << 20);
 }
 
 static dgmi::RhsArgs mix_args(dgmi_ctx *c, int N) {

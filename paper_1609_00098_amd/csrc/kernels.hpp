@@ -53,7 +53,7 @@ struct RhsArgs {
   double a, b, dt;     // Shu-Osher stage: out = a Un + b (U + dt L(U))
   int nx, ny, nz;      // elements per direction
   int streamed;        // stage kernel: U^n is read and the output written past the caches (set where a stage's
-                       // arrays exceed the last-level cache)
+                       // arrays are well beyond the last-level cache)
   int full_prims;      // stage kernel: write all five primitive rows (else NE/SR only p, SRMHD on uniform
                        // meshes p and, in row 0, the magnetic cubic's root em)
   int in_pe;           // uniform SRMHD stage: the input's primitives are such a (p, em) pair
