@@ -74,7 +74,7 @@ __global__ void __launch_bounds__((LimCfg<SYS, N>::THREADS)) limiter_moments_ker
   using C = LimCfg<SYS, N>;
   constexpr int NP = C::NP, NPE = C::NPE, NF = C::NF, NV = C::NV, EPB = C::EPB;
   __shared__ double su[EPB * NV * NPE];
-  __shared__ double lines[EPB * NV * (4 * NF + NP)];
+  __shared__ double lines[4 * EPB * NV * NF];
   __shared__ double sh[NP], smu[NP];
   __shared__ int sbad[EPB];
   const int tid = threadIdx.x;

@@ -30,7 +30,7 @@ __device__ __forceinline__ double minmodB(double a1, double a2, double a3, doubl
 // the first-moment weights are odd about the element centre, so a line on
 // which U is constant gives exactly zero) and its two end values; those over
 // y to plane sums; those over z.  sh = w/2 and smu = 3/2 int(ell xi) per node
-// index (LDS); lines: LDS scratch of EPB NV (4 (N+1)^2 + N+1) doubles; su is
+// index (LDS); lines: LDS scratch of 4 EPB NV (N+1)^2 doubles; su is
 // overwritten.  The block holds slots e0 .. e0+EPB-1 of nelem; slot k is
 // element eids[k] (mixed-degree lists) or k itself (eids null).  Every thread
 // of the block must call it.
@@ -39,7 +39,9 @@ __device__ __forceinline__ void element_moments(double *su, double *lines, const
                                                 double *mom, int64_t e0, int64_t nelem, const int32_t *eids = nullptr) {
   constexpr int NP = N + 1, NF = NP * NP, NPE = NP * NF;
   const int tid = threadIdx.x;
-  double *const slopes = lines + EPB * NV * 4 * NF;  // [EPB NV][NP] y-pair sums of A per plane
+  // rows of plane sums: A, B, the end values and, where su has room, the y-pair
+  // sums of A (at degree 1 the last level forms those, one pair per plane)
+  constexpr int ROWS = N >= 2 ? 5 : 4;
   for (int t = tid; t < EPB * NV * NF; t += BT) {
     const int le = t / (NV * NF), r = t - le * NV * NF, v = r / NF, jk = r - v * NF;
     if (e0 + le >= nelem) continue;
@@ -56,22 +58,21 @@ __device__ __forceinline__ void element_moments(double *su, double *lines, const
     L[3 * NF + jk] = line[N];
   }
   __syncthreads();
-  // planes of constant z: weighted sums over y of A, B and the end values into
-  // su as [element, component][4][NP], and the y-slope sums of A
-  for (int t = tid; t < EPB * NV * 5 * NP; t += BT) {
-    const int c = t / (5 * NP), r = t - c * 5 * NP, x = r / NP, k = r - x * NP;
+  // planes of constant z: weighted sums over y of A, B and the end values, and
+  // the y-pair sums of A, into su as [element, component][ROWS][NP]
+  for (int t = tid; t < EPB * NV * ROWS * NP; t += BT) {
+    const int c = t / (ROWS * NP), r = t - c * ROWS * NP, x = r / NP, k = r - x * NP;
     if (e0 + c / NV >= nelem) continue;
     const double *X = lines + c * 4 * NF + (x < 4 ? x * NF : 0) + NP * k;
     double s = 0.0;
     if (x < 4) {
 #pragma unroll
       for (int j = 0; j < NP; ++j) s += sh[j] * X[j];
-      su[c * NPE + x * NP + k] = s;
     } else {
 #pragma unroll
       for (int j = 0; j < N - j; ++j) s += smu[N - j] * (X[N - j] - X[j]);
-      slopes[c * NP + k] = s;
     }
+    su[c * NPE + x * NP + k] = s;
   }
   __syncthreads();
   for (int t = tid; t < EPB * NV * 10; t += BT) {
@@ -85,10 +86,12 @@ __device__ __forceinline__ void element_moments(double *su, double *lines, const
       for (int k = 0; k < N - k; ++k) s += smu[N - k] * (R[N - k] - R[k]);
     } else if (kind >= 8) {  // the z faces are planes
       s = R[kind == 8 ? 0 : N];
+    } else if (N == 1 && kind == 2) {
+#pragma unroll
+      for (int k = 0; k < NP; ++k) s += sh[k] * (smu[N] * (A[N + NP * k] - A[NP * k]));
     } else {
       // mean, c_x, c_y, x faces: plane sums; y faces: the x-line sums at j = 0, N
-      const double *X = kind == 2 ? slopes + c * NP
-                                  : (kind >= 6 ? A + (kind == 6 ? 0 : N) : R + NP * (kind < 2 ? kind : kind - 2));
+      const double *X = kind >= 6 ? A + (kind == 6 ? 0 : N) : R + NP * (kind == 2 ? 4 : (kind < 2 ? kind : kind - 2));
       const int st = kind >= 6 ? NP : 1;
 #pragma unroll
       for (int k = 0; k < NP; ++k) s += sh[k] * X[k * st];
