@@ -19,8 +19,10 @@
 //      first round thus overlap the own-node loads instead of following the
 //      volume work.
 //   3. Volume term, one direction at a time: each thread takes its state
-//      back from the buffer, writes its flux along d there, and contracts
-//      its pencil with its row of D (eq. for D^{1bar}), scaled by 2/dx_d.
+//      back from the buffer and writes its flux along d there; the lines along
+//      d are contracted with D (eq. for D^{1bar}), a lane per line in place
+//      where one round of lanes covers them, else each thread its own node's
+//      pencil; scaled by 2/dx_d.
 //   4. Each volume thread adds -(2/dx_d)(1/w_end)(F*.n - F.n) for every face
 //      it lies on (edge and corner nodes receive two or three terms).
 //   5. RHS mode writes dU/dt; stage mode forms the Shu-Osher combination
@@ -138,25 +140,6 @@ struct RhsCfg {
   static constexpr int SLOT = EPB * NV * 6 * NF;
   static constexpr int LDS = VOL + SLOT + NP * NP;  // doubles
 };
-
-// A node's conserved state and primitives.  SRMHD reads all five primitive
-// rows; SR reads only the pressure and NE no primitive at all: the rest
-// follows from U (and p) in closed form, exactly as the recovery returned it.
-template <int SYS>
-__device__ __forceinline__ void load_node(const double *U, const double *Pr, int64_t nn, int64_t q, double g,
-                                          double *u, Prim &P, bool poly = false) {
-#pragma unroll
-  for (int v = 0; v < SysTraits<SYS>::nv; ++v) u[v] = U[v * nn + q];
-  if (SYS == kMHD) {
-    P.rho = Pr[q];
-    P.v[0] = Pr[nn + q];
-    P.v[1] = Pr[2 * nn + q];
-    P.v[2] = Pr[3 * nn + q];
-    P.p = Pr[4 * nn + q];
-  } else {
-    P = prims_at_pressure<SYS>(u, g, SYS == kSR ? Pr[4 * nn + q] : 0.0, poly);
-  }
-}
 
 // Tables that no kernel writes, read at wave-uniform addresses through the
 // scalar cache.
@@ -578,7 +561,12 @@ __device__ __forceinline__ void rhs_body(const RhsArgs &A, int grp, double *smem
   // of the SR operator's 112 us (32^3 elements of degree 4); 99.5 us now.  With
   // a second, partly filled round the lane per node is faster: SRMHD degree 3,
   // 288 lines on 192 threads, 3.92 against 3.99 ms a step; SR degree 3, 320 on
-  // 256, 112 against 124 us.
+  // 256, 112 against 124 us.  Where the rule takes lines (NE and SR from degree 4,
+  // SRMHD degree 5, 9 of the 21 tiles of the mixed launch) no operator got slower
+  // than by node, us for 2x10^6 nodes by line / node: NE 46.5 / 51.6 at degree 4,
+  // 49.5 / 58.7, 49.6 / 60.8, 52.8 / 57.1 at 7; SR 51.2 / 55.8, 53.7 / 61, 51 / 64,
+  // 55.3 / 59.2; SRMHD 122 / 131.  (At degree 7 the lines along x start 8 doubles
+  // apart and share banks: the least gain.)
   constexpr int LINES = EPB * NV * NF;
   constexpr bool BY_LINE = LINES <= BT;
   scalar_f64 *const Dm = (scalar_f64 *)A.Dmat;
