@@ -7,7 +7,7 @@
 // step have their times known at its start: one launch fills a copy of the
 // buffer for each (three launches of 10 us, bound by the exponentials' and
 // powers' dependent chains, were 30 of 82 us of a step of 32 x 32 elements of
-// degree 5; now one of 12 us, 68 us a step).
+// degree 5; now one of 16 us under the kernel trace, 68 us a step).
 //
 // Layout of the buffer: box face f = 2d + side holds the elements of that
 // face ordered (a, b) over the two other directions in increasing order,

@@ -23,10 +23,13 @@
 // Between RK stages only the pressure row of the primitives is read (NE, SR),
 // so only that row is written there (full_prims of LimArgs).  A limited step
 // of 32^3 SR elements of degree 4, half of the components troubled, took
-// 1,039 us with all five rows written everywhere, a launch of its own for the
-// decisions and moments summed a face per thread, 870 us now (stage 250 -> 190
-// us, decisions and rewrite 106 -> 100 us, bound by the recovery's vector
-// instructions and the chain of neighbour loads in front of it).
+// 1,112 us with all five rows written everywhere, a launch of its own for the
+// decisions and moments summed a face per thread, 870 us without (stage 250 ->
+// 190 us, decisions and rewrite 106 -> 100 us, bound by the recovery's vector
+// instructions and the chain of neighbour loads in front of it), and 830 us
+// with the steps since.  (dg_limit alone gains less: 161 us before and 166 now on
+// 26^3 SR elements of degree 5, where five of 256 threads decide; 222 and 188 on
+// 53^3 of degree 2.)
 //
 // Per component k of element e and direction d (every direction has degree
 // N >= 1 on a uniform mesh):

@@ -730,7 +730,7 @@ DG_HD bool mhd_f0(const double *u, double g, double *f, double *em_out, double *
 // (tol > 0), else polish mode.
 //
 // Bound by vector issue.  With the cubic's start and stop above and the modes
-// compiled apart, SRMHD to 1e-10 from the f(0) seed takes 781 us for 2.5e7 points
+// compiled apart, SRMHD to 1e-10 from the f(0) seed takes 742 us for 2.5e7 points
 // (980 before).  Polish mode keeps no more of the smallest |f| than the value and
 // its pressure, and tests it afterwards.  (A first loop without that record, and
 // the points beyond 16 evaluations started over with it, was as fast where all

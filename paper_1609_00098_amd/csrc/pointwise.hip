@@ -92,10 +92,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GUESS 
 
 // NE and SR seeded from the input pressure (GUESS 0) or the bracket
 // (GUESS 1): two points per thread, both loaded before either is recovered,
-// so that the second point's loads overlap the first point's iteration (71
-// VGPRs, seven waves per SIMD; SRMHD's longer recovery keeps one point per
-// thread, where the second point's registers cost more occupancy than the
-// overlap gains).
+// so that the second point's loads overlap the first point's iteration (SR from
+// the input pressure 66 VGPRs and seven waves per SIMD to a tolerance, 76 and six
+// polished; SRMHD's longer recovery keeps one point per thread, where the second
+// point's registers cost more occupancy than the overlap gains).
 template <int SYS, int GUESS, bool TOL>
 __global__ void __launch_bounds__(256) con2prim2_kernel(const C2PArgs A) {
   static_assert(SYS != kMHD && GUESS <= 1, "NE / SR, input or bracket seed");
